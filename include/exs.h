@@ -72,11 +72,11 @@ const char* exs_last_error(void);
  *               centre, where each ligand's centroid is placed.
  *   storage     EXS_F32, EXS_BF16 or EXS_F16: texels are stored in this type
  *               (round to nearest even); interpolation and accumulation run in
- *               FP32.  The search reads a copy expanded per cell: the 8
- *               corners of every cell together (32 B FP32, 16 B 16-bit), so a
- *               lookup is one contiguous block; this costs 8x (FP32) or 4x
- *               (16-bit) the bytes of the input, and each channel's expanded
- *               copy must stay below 2 GiB.  The FP32 master copy is always
+ *               FP32.  The search reads a copy that keeps, for every node, the four
+ *               texels of its y-z square, so that a cell's 8 corners are one run of 32 B
+ *               (FP32) or 16 B (16-bit): 4x (FP32) or 2x (16-bit) the bytes of the input.
+ *               A channel's cells, at 32 B (FP32) or 16 B (16-bit) each, must stay below
+ *               2 GiB.  The FP32 master copy is always
  *               kept as well: it feeds the FP64 rescoring of the top poses.
  *   pocket_id_out  receives the handle.
  * Errors: EXS_EINVAL (bad sizes, nx * ny or nz of 2^23 or more, channels >
@@ -143,7 +143,7 @@ int exs_get_rescored_poses(int64_t job, int wait, double* score2, int32_t* best_
                            double* best_score2);
 
 /*
- * Gather probe: the docking kernels' texel lookup (same per-cell blocks, loads and FP32
+ * Gather probe: the docking kernels' texel lookup (same texel layout, loads and FP32
  * trilinear arithmetic) alone, to measure the lookup rate the search is held against
  * (Sec. 3.1: the score of a pose is a lookup per atom in the pocket's grids).
  * n_lanes lanes (rounded up to a multiple of 256) each do lookups_per_lane lookups (rounded
@@ -236,7 +236,9 @@ int exs_pack_topology(int n, const float* x, const float* y, const float* z, con
  *                  closer than the cutoff
  *   top_k          0, or 1..EXS_MAX_TOPK: rescore each ligand's top_k poses in
  *                  FP64 from the FP32 master grid and pick the best by FP64
- *   poses_per_lane 0 = auto, or 1, 2, 4 (orientations searched by one lane)
+ *   poses_per_lane 0 = auto, or 1, 2, 4: share of a ligand's orientations that one wave
+ *                  searches (1: the least, a workgroup has the most waves; the results are
+ *                  the same)
  *   ligands_per_wg 0 = auto, or 1, 2, 4, 8 (ligands per workgroup)
  *   flags          EXS_FLAG_* bits
  *   cluster_rmsd_A, rank_keep   ranking of each ligand's K final poses (Sec. 3.1,

@@ -4,24 +4,24 @@
 
 namespace exs {
 
-hipError_t launch_dock_f16(const DockArgs& a, int ppl, dim3 grid, dim3 block, size_t lds,
+hipError_t launch_dock_f16(const DockArgs& a, int lanes, dim3 grid, dim3 block, size_t lds,
                            hipStream_t st) {
-#define EXS_LAUNCH(SS, PP) \
-    if (a.S == SS && ppl == PP) { \
-        hipLaunchKernelGGL((dock_kernel<SS, PP, TexF16>), grid, block, lds, st, a); \
+#define EXS_LAUNCH(SS, GG) \
+    if (a.S == SS && lanes == GG) { \
+        hipLaunchKernelGGL((dock_kernel<SS, GG, TexF16>), grid, block, lds, st, a); \
         return hipGetLastError(); \
     }
-    EXS_LAUNCH(8, 1) EXS_LAUNCH(8, 2) EXS_LAUNCH(8, 4) EXS_LAUNCH(16, 1) EXS_LAUNCH(16, 2)
-    EXS_LAUNCH(16, 4) EXS_LAUNCH(32, 1) EXS_LAUNCH(32, 2) EXS_LAUNCH(32, 4)
+    EXS_LAUNCH(8, 4) EXS_LAUNCH(8, 8) EXS_LAUNCH(16, 4) EXS_LAUNCH(16, 8) EXS_LAUNCH(16, 16)
+    EXS_LAUNCH(32, 4) EXS_LAUNCH(32, 8) EXS_LAUNCH(32, 16)
 #undef EXS_LAUNCH
     return hipErrorInvalidValue;
 }
 
-const void* dock_kernel_fn_f16(int S, int ppl) {
-#define EXS_FN(SS, PP) \
-    if (S == SS && ppl == PP) return reinterpret_cast<const void*>(&dock_kernel<SS, PP, TexF16>);
-    EXS_FN(8, 1) EXS_FN(8, 2) EXS_FN(8, 4) EXS_FN(16, 1) EXS_FN(16, 2) EXS_FN(16, 4)
-    EXS_FN(32, 1) EXS_FN(32, 2) EXS_FN(32, 4)
+const void* dock_kernel_fn_f16(int S, int lanes) {
+#define EXS_FN(SS, GG) \
+    if (S == SS && lanes == GG) return reinterpret_cast<const void*>(&dock_kernel<SS, GG, TexF16>);
+    EXS_FN(8, 4) EXS_FN(8, 8) EXS_FN(16, 4) EXS_FN(16, 8) EXS_FN(16, 16)
+    EXS_FN(32, 4) EXS_FN(32, 8) EXS_FN(32, 16)
 #undef EXS_FN
     return nullptr;
 }

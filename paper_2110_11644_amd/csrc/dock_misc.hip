@@ -11,12 +11,12 @@
 
 namespace exs {
 
-hipError_t launch_dock_f32(const DockArgs& a, int ppl, dim3 grid, dim3 block, size_t lds, hipStream_t st);
-hipError_t launch_dock_bf16(const DockArgs& a, int ppl, dim3 grid, dim3 block, size_t lds, hipStream_t st);
-hipError_t launch_dock_f16(const DockArgs& a, int ppl, dim3 grid, dim3 block, size_t lds, hipStream_t st);
-const void* dock_kernel_fn_f32(int S, int ppl);
-const void* dock_kernel_fn_bf16(int S, int ppl);
-const void* dock_kernel_fn_f16(int S, int ppl);
+hipError_t launch_dock_f32(const DockArgs& a, int lanes, dim3 grid, dim3 block, size_t lds, hipStream_t st);
+hipError_t launch_dock_bf16(const DockArgs& a, int lanes, dim3 grid, dim3 block, size_t lds, hipStream_t st);
+hipError_t launch_dock_f16(const DockArgs& a, int lanes, dim3 grid, dim3 block, size_t lds, hipStream_t st);
+const void* dock_kernel_fn_f32(int S, int lanes);
+const void* dock_kernel_fn_bf16(int S, int lanes);
+const void* dock_kernel_fn_f16(int S, int lanes);
 hipError_t upload_trig_f32(const float* t32, const double* t64);
 hipError_t upload_trig_bf16(const float* t32, const double* t64);
 hipError_t upload_trig_f16(const float* t32, const double* t64);
@@ -39,60 +39,24 @@ __device__ __forceinline__ uint32_t to16(float v, int storage) {
     return (uint32_t)__builtin_bit_cast(uint16_t, (_Float16)v);   // FP16
 }
 
-// Expand the FP32 master [C][nz][ny][nx] (x fastest) into the per-cell gather layout, one
-// 16-byte entry per thread; cx = nx-1, cy = ny-1, cz = nz-1 cells, corner index dx + 2 dy + 4 dz.
-// FP32 cells are indexed (z * cy + y) * cx + x; 16-bit cells go in 2 x 2 x 2 bricks (bricks x
-// fastest, cell 4 (z & 1) + 2 (y & 1) + (x & 1) within a brick; cells of an odd edge's padding
-// are zero and never read).
-//  FP32 (storage 0): two entries per cell, entry dz = {V(x,y,z+dz), V(x+1,y,z+dz) - V(x,y,z+dz),
-//  V(x,y+1,z+dz), V(x+1,y+1,z+dz) - V(x,y+1,z+dz)} (x differences rounded in FP32, as the
-//  interpolation's x round would compute them).
-//  16-bit (1 BF16, 2 FP16): one entry per cell, dword j = corner(2j) | corner(2j+1) << 16.
-__global__ void expand_grid_kernel(const float* __restrict__ src, uint4* __restrict__ dst,
-                                   int nx, int ny, int nz, int64_t per_chan, int64_t count,
-                                   int storage) {
-    const int cx = nx - 1, cy = ny - 1;
-    const int64_t nxy = (int64_t)nx * ny, chan = nxy * nz;
-    const int per_cell = storage == 0 ? 2 : 1;
-    const int cz = nz - 1, bxc = nx / 2, byc = ny / 2;   // 16-bit: bricks per row and per column
+// Expand the FP32 master [C][nz][ny][nx] (x fastest) into the gather layout, one entry per thread:
+// entry (x, y, z), index (z * (ny-1) + y) * nx + x, holds the texels of the y-z square of the node,
+// V(y, z), V(y+1, z), V(y, z+1), V(y+1, z+1) at x, as four floats (storage 0) or as four 16-bit
+// values (1 BF16, 2 FP16, rounded to nearest even).
+__global__ void expand_grid_kernel(const float* __restrict__ src, void* __restrict__ dst, int nx, int ny,
+                                   int64_t nxyz, int64_t per_chan, int64_t count, int storage) {
+    const int64_t nxy = (int64_t)nx * ny;
     for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < count;
          i += (int64_t)gridDim.x * blockDim.x) {
         const int64_t c = i / per_chan, e = i - c * per_chan;
-        const int64_t cell = e / per_cell;
-        const int half = (int)(e - cell * per_cell);
-        int x, y, z;
-        if (storage == 0) {
-            x = (int)(cell % cx);
-            const int64_t yz = cell / cx;
-            y = (int)(yz % cy); z = (int)(yz / cy);
-        } else {
-            const int64_t brick = cell >> 3;
-            const int sub = (int)(cell & 7);
-            x = (int)(brick % bxc) * 2 + (sub & 1);
-            const int64_t rest = brick / bxc;
-            y = (int)(rest % byc) * 2 + ((sub >> 1) & 1);
-            z = (int)(rest / byc) * 2 + (sub >> 2);
-            if (x >= cx || y >= cy || z >= cz) {   // padding of an odd edge: never read
-                dst[i] = make_uint4(0u, 0u, 0u, 0u);
-                continue;
-            }
-        }
-        const float* b = src + c * chan + (int64_t)z * nxy + (int64_t)y * nx + x;
-        uint4 o;
-        if (storage == 0) {
-            const float* q = b + half * nxy;
-            const float d0 = q[1] - q[0], d1 = q[nx + 1] - q[nx];   // x differences, FP32
-            o = make_uint4(__builtin_bit_cast(uint32_t, q[0]), __builtin_bit_cast(uint32_t, d0),
-                           __builtin_bit_cast(uint32_t, q[nx]), __builtin_bit_cast(uint32_t, d1));
-        } else {
-            uint32_t w[4];
-            for (int j = 0; j < 4; ++j) {
-                const float* r = b + (j >> 1) * nxy + (j & 1) * nx;   // (dy, dz) = (j & 1, j >> 1)
-                w[j] = to16(r[0], storage) | (to16(r[1], storage) << 16);
-            }
-            o = make_uint4(w[0], w[1], w[2], w[3]);
-        }
-        dst[i] = o;
+        const int64_t row = e / nx, z = row / (ny - 1);
+        const float* q = src + c * nxyz + z * nxy + (row - z * (ny - 1)) * nx + (e - row * nx);
+        const float v0 = q[0], v1 = q[nx], v2 = q[nxy], v3 = q[nxy + nx];
+        if (storage == 0)
+            static_cast<float4*>(dst)[i] = make_float4(v0, v1, v2, v3);
+        else
+            static_cast<uint2*>(dst)[i] = make_uint2(to16(v0, storage) | (to16(v1, storage) << 16),
+                                                     to16(v2, storage) | (to16(v3, storage) << 16));
     }
 }
 
@@ -102,13 +66,13 @@ __global__ void zero_ints_kernel(int* p, int n) {
     if (i < n) p[i] = 0;
 }
 
-hipError_t launch_dock(const DockArgs& a, int storage, int ppl, int n_blocks, int threads,
-                       size_t lds, hipStream_t st) {
-    dim3 grid(n_blocks), block(threads);
+hipError_t launch_dock(const DockArgs& a, int storage, const DockShape& sh, int n_blocks, hipStream_t st) {
+    const dim3 grid(n_blocks), block(sh.waves * kWave);
+    const size_t lds = (size_t)sh.lds.total;
     switch (storage) {
-        case 0: return launch_dock_f32(a, ppl, grid, block, lds, st);
-        case 1: return launch_dock_bf16(a, ppl, grid, block, lds, st);
-        case 2: return launch_dock_f16(a, ppl, grid, block, lds, st);
+        case 0: return launch_dock_f32(a, sh.lanes, grid, block, lds, st);
+        case 1: return launch_dock_bf16(a, sh.lanes, grid, block, lds, st);
+        case 2: return launch_dock_f16(a, sh.lanes, grid, block, lds, st);
         default: return hipErrorInvalidValue;
     }
 }
@@ -123,29 +87,28 @@ hipError_t launch_gather_probe(const GridDesc* gd, int storage, int nb, int64_t 
     }
 }
 
-const void* dock_kernel_fn(int storage, int S, int ppl) {
+const void* dock_kernel_fn(int storage, int S, int lanes) {
     switch (storage) {
-        case 0: return dock_kernel_fn_f32(S, ppl);
-        case 1: return dock_kernel_fn_bf16(S, ppl);
-        case 2: return dock_kernel_fn_f16(S, ppl);
+        case 0: return dock_kernel_fn_f32(S, lanes);
+        case 1: return dock_kernel_fn_bf16(S, lanes);
+        case 2: return dock_kernel_fn_f16(S, lanes);
         default: return nullptr;
     }
 }
 
-int64_t expanded_entries(int nx, int ny, int nz, int storage) {
-    if (storage == 0) return (int64_t)(nx - 1) * (ny - 1) * (nz - 1) * 2;
-    return (int64_t)8 * (nx / 2) * (ny / 2) * (nz / 2);
+int64_t expanded_bytes(int nx, int ny, int nz, int storage) {
+    return (int64_t)nx * (ny - 1) * (nz - 1) * (storage == 0 ? 16 : 8);
 }
 
 hipError_t launch_expand_grid(const float* src, void* dst, int nx, int ny, int nz, int channels,
                               int storage, hipStream_t st) {
-    const int64_t per_chan = expanded_entries(nx, ny, nz, storage);
+    const int64_t per_chan = (int64_t)nx * (ny - 1) * (nz - 1);
     const int64_t count = per_chan * channels;
     int64_t blocks = (count + 255) / 256;
     if (blocks > 65536) blocks = 65536;
     if (blocks < 1) blocks = 1;
     hipLaunchKernelGGL(expand_grid_kernel, dim3((unsigned)blocks), dim3(256), 0, st, src,
-                       static_cast<uint4*>(dst), nx, ny, nz, per_chan, count, storage);
+                       dst, nx, ny, (int64_t)nx * ny * nz, per_chan, count, storage);
     return hipGetLastError();
 }
 
@@ -232,7 +195,13 @@ hipError_t launch_stage_ints(const int32_t* src, int32_t* dst, int n, int* zero,
 // phi_k = k * golden angle, rows of the product in FP64 and rounded to FP32.  Computed on the
 // device so that every launch path (and a path that cannot allocate or copy from the host)
 // reads the same table bit for bit.
-__global__ void orientation_table_kernel(int K, float* __restrict__ r32, double* __restrict__ r64) {
+__host__ __device__ inline int orientation_bands(int K) {
+    int b = 1;   // round(sqrt(K) / 7): a wave's patch about as high as it is wide
+    while ((2 * b + 1) * (2 * b + 1) * 49 <= 4 * K) ++b;
+    return b;
+}
+__global__ void orientation_table_kernel(int K, float* __restrict__ r32, double* __restrict__ r64,
+                                         int32_t* __restrict__ order_k) {
     const int k = blockIdx.x * blockDim.x + threadIdx.x;
     if (k >= K) return;
     const double golden = 3.14159265358979323846 * (3.0 - sqrt(5.0));
@@ -244,10 +213,24 @@ __global__ void orientation_table_kernel(int K, float* __restrict__ r32, double*
         if (r64) r64[(size_t)k * 9 + t] = m[t];
         r32[(size_t)k * 9 + t] = (float)m[t];
     }
+    // Order of the chunks: bands of consecutive k (consecutive z), by azimuth within a band, so
+    // that the orientations of a wave are neighbours and its lookups share lines.  The azimuth in
+    // turns as a 32-bit fraction (integer arithmetic: every thread sees the same order).
+    const int bands = orientation_bands(K);
+    const int b = (int)((int64_t)k * bands / K);
+    const int k0 = (int)(((int64_t)b * K + bands - 1) / bands), k1 = (int)(((int64_t)(b + 1) * K + bands - 1) / bands);
+    constexpr uint32_t kGoldenTurn = 1640531527u;   // round((3 - sqrt 5) / 2 * 2^32)
+    const uint32_t mine = (uint32_t)k * kGoldenTurn;
+    int at = k0;
+    for (int j = k0; j < k1; ++j) {
+        const uint32_t p = (uint32_t)j * kGoldenTurn;
+        at += p < mine || (p == mine && j < k) ? 1 : 0;
+    }
+    order_k[at] = k;
 }
 
-hipError_t launch_orientation_table(int K, float* r32, double* r64, hipStream_t st) {
-    hipLaunchKernelGGL(orientation_table_kernel, dim3((K + 63) / 64), dim3(64), 0, st, K, r32, r64);
+hipError_t launch_orientation_table(int K, float* r32, double* r64, int32_t* order_k, hipStream_t st) {
+    hipLaunchKernelGGL(orientation_table_kernel, dim3((K + 63) / 64), dim3(64), 0, st, K, r32, r64, order_k);
     return hipGetLastError();
 }
 

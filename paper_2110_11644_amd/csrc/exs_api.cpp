@@ -54,7 +54,8 @@ int fail(int code, const char* fmt, ...) {
 struct DeviceState {
     bool ready = false;
     int cus = 0;
-    std::map<int, std::pair<float*, double*>> orient_tables;   // K -> (FP32, FP64) [K][9]
+    struct Orient { float* r32; double* r64; int32_t* order; };
+    std::map<int, Orient> orient_tables;   // K -> matrices [K][9] in FP32 and FP64, chunk order [K]
 };
 
 std::mutex g_dev_mu;
@@ -85,21 +86,22 @@ int ensure_device(int dev) {
 
 // Fibonacci-sphere orientation tables of K orientations, built once per (device, K) by
 // orientation_table_kernel (the no-allocation entry point builds the same table on the device).
-int orientation_tables(int dev, int K, const float** r32, const double** r64) {
+int orientation_tables(int dev, int K, const float** r32, const double** r64, const int32_t** order) {
     std::lock_guard<std::mutex> lk(g_dev_mu);
     DeviceState& d = g_dev[dev];
     auto it = d.orient_tables.find(K);
     if (it == d.orient_tables.end()) {
-        float* d32 = nullptr;
-        double* d64 = nullptr;
-        HIP_TRY(hipMalloc(&d32, (size_t)K * 9 * sizeof(float)));
-        HIP_TRY(hipMalloc(&d64, (size_t)K * 9 * sizeof(double)));
-        HIP_TRY(launch_orientation_table(K, d32, d64, nullptr));
+        DeviceState::Orient t{};
+        HIP_TRY(hipMalloc(&t.r32, (size_t)K * 9 * sizeof(float)));
+        HIP_TRY(hipMalloc(&t.r64, (size_t)K * 9 * sizeof(double)));
+        HIP_TRY(hipMalloc(&t.order, (size_t)K * sizeof(int32_t)));
+        HIP_TRY(launch_orientation_table(K, t.r32, t.r64, t.order, nullptr));
         HIP_TRY(hipStreamSynchronize(nullptr));
-        it = d.orient_tables.emplace(K, std::make_pair(d32, d64)).first;
+        it = d.orient_tables.emplace(K, t).first;
     }
-    *r32 = it->second.first;
-    *r64 = it->second.second;
+    *r32 = it->second.r32;
+    *r64 = it->second.r64;
+    *order = it->second.order;
     return EXS_OK;
 }
 
@@ -120,7 +122,7 @@ struct Pocket {
     int nx = 0, ny = 0, nz = 0, channels = 0, storage = EXS_F32;
     double h = 0, origin[3] = {0, 0, 0};
     float* master = nullptr;     // FP32 texels
-    void* tex = nullptr;         // per-cell gather layout (8 corners per cell)
+    void* tex = nullptr;         // gather layout (the four texels of each node's y-z square)
     GridDesc desc;
     std::atomic<int> users{0};
 };
@@ -137,7 +139,7 @@ struct Plan {
 
 struct Batch {
     int device = 0;
-    int L = 0, A = 0, R = 0, n_max = 1;
+    int L = 0, A = 0, R = 0, n_max = 1, rot_max = 0;
     std::vector<int32_t> pockets;          // pocket handle per table slot
     std::vector<int> storage_of_slot;
     std::vector<LigInfo> info;             // host copy
@@ -226,12 +228,23 @@ int fail(int code, const char* fmt, ...) {
 }
 int current_device(int* dev) { return ::current_device(dev); }
 int ensure_device(int dev) { return ::ensure_device(dev); }
-int orientation_tables(int dev, int K, const float** r32, const double** r64) {
-    return ::orientation_tables(dev, K, r32, r64);
+int orientation_tables(int dev, int K, const float** r32, const double** r64, const int32_t** order) {
+    return ::orientation_tables(dev, K, r32, r64, order);
 }
 int device_cus(int dev) {
     std::lock_guard<std::mutex> lk(g_dev_mu);
     return g_dev[dev].cus;
+}
+int resident_workgroups(int dev, int storage, int S, const DockShape& sh, int* out) {
+    const void* fn = dock_kernel_fn(storage, S, sh.lanes);
+    if (!fn) return fail(EXS_EINVAL, "no kernel for this configuration");
+    if (sh.lds.total > 64 * 1024)
+        HIP_TRY(hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, sh.lds.total));
+    int per_cu = 0;
+    hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, fn, sh.waves * kWave, sh.lds.total);
+    if (e != hipSuccess || per_cu < 1) per_cu = 1;
+    *out = per_cu * std::max(1, device_cus(dev));
+    return EXS_OK;
 }
 bool pocket_info(int32_t id, PocketInfo* out) {
     auto p = find_pocket(id);
@@ -249,6 +262,56 @@ void pocket_use(int32_t id, int delta) {
 }
 
 }  // namespace rt
+
+// Waves of a workgroup that fit on a CU: LDS in its allocation granules, and the registers that
+// the dock kernels are held to.
+static int dock_waves_per_cu(int lds, int waves) {
+    constexpr int kGranule = 1280, kRegisterWaves = 12;
+    const int by_lds = (int)kMaxLdsBytes / ((lds + kGranule - 1) / kGranule * kGranule);
+    return std::min(by_lds, kRegisterWaves / waves) * waves;
+}
+
+// Lanes per orientation, waves per workgroup and workgroups per ligand of a launch of n_lig
+// ligands.  Four lanes per orientation do the least work; where the launch then leaves SIMDs
+// without a wave, more lanes (and a wave per chunk) shorten the chain of a chunk.
+DockShape dock_shape(int n_lig, int n_max, int rot_max, int K, int S, int top_k, int lpw, int ppl, int cus) {
+    DockShape sh;
+    const int64_t room = (int64_t)8 * std::max(1, cus);   // waves: two per SIMD
+    auto chunks_of = [&](int lanes) { return (K * lanes + kWave - 1) / kWave; };
+    sh.lanes = 4;
+    for (int lanes : {16, 8})
+        if (lanes <= S && (int64_t)n_lig * chunks_of(lanes) <= room) { sh.lanes = lanes; break; }
+    const int chunks = chunks_of(sh.lanes), items = lpw * chunks;
+    const int64_t total = (int64_t)n_lig * chunks;
+    auto lds_of = [&](int w) { return dock_lds(lpw, n_max, rot_max, top_k, w, sh.lanes, S); };
+    if (lpw == 1 && total <= room) {   // every chunk runs at once: spread over the CUs
+        sh.waves = total <= 2 * std::max(1, cus) ? 1 : (total <= 4 * std::max(1, cus) ? 2 : 4);
+        sh.waves = std::min(sh.waves, chunks);
+        while (sh.waves > 1 && lds_of(sh.waves).total > kDockLdsBytes) --sh.waves;
+        sh.parts = (chunks + sh.waves - 1) / sh.waves;
+    } else {
+        // the workgroup size with the most waves on a CU, less the rounds its waves do not fill
+        double best = -1.0;
+        for (int w = 1; w <= std::min(kMaxWavesPerWg, items); ++w) {
+            const int lds = lds_of(w).total;
+            if (lds > kDockLdsBytes) break;
+            const double eff = (double)items / (double)((items + w - 1) / w * w);
+            const double score = eff * dock_waves_per_cu(lds, w);
+            if (score >= best) { best = score; sh.waves = w; }
+        }
+        sh.waves = std::max(1, sh.waves / ppl);
+        if (lpw == 1) {
+            // a wave takes `each` chunks one after another; the launch is as long as its largest
+            // ligand's when that is more than about a quarter of the chunks per wave slot
+            const int64_t slots = (int64_t)std::max(1, cus) * std::max(1, dock_waves_per_cu(lds_of(sh.waves).total, sh.waves));
+            const int64_t each = std::max<int64_t>(1, total / (4 * slots));
+            sh.parts = (int)std::max<int64_t>(1, chunks / (sh.waves * each));
+        }
+    }
+    sh.lds = lds_of(sh.waves);
+    return sh;
+}
+
 }  // namespace exs
 
 // ---- C ABI -------------------------------------------------------------------------------------
@@ -274,9 +337,13 @@ int exs_load_pocket_grid(const float* values, int nx, int ny, int nz, int channe
             return fail(EXS_EINVAL, "grid %dx%dx%d: nx*ny and nz must be below 2^23 (cell offsets use 24-bit multiplies)",
                         nx, ny, nz);
         const int64_t chan = (int64_t)nx * ny * nz;
-        const int64_t tex_chan_bytes = expanded_entries(nx, ny, nz, storage) * 16;
-        if (tex_chan_bytes > INT32_MAX)
+        // the limit counts whole cells (32 B in FP32; 16 B in 2 x 2 x 2 groups in 16 bits), never
+        // less than the gather layout takes
+        const int64_t limit_bytes = storage == EXS_F32 ? (int64_t)(nx - 1) * (ny - 1) * (nz - 1) * 32
+                                                       : (int64_t)(nx / 2) * (ny / 2) * (nz / 2) * 128;
+        if (limit_bytes > INT32_MAX)
             return fail(EXS_EINVAL, "a grid channel must expand to < 2 GiB (32 B per FP32 cell, 16 B per 16-bit cell)");
+        const int64_t tex_chan_bytes = expanded_bytes(nx, ny, nz, storage);
         const int64_t count = chan * channels;
         if (!values_on_device) {
             for (int64_t i = 0; i < count; ++i) {
@@ -516,7 +583,10 @@ int exs_upload_ligands(const exs_ligand_batch* in, void* stream, int64_t* batch_
         }
         for (int l = 0; l < L; ++l)
             if (rc_of[l]) return fail(rc_of[l], "ligand %d: %s", l, err_of[l].c_str());
-        for (int l = 0; l < L; ++l) b->n_max = std::max<int>(b->n_max, b->info[l].n);
+        for (int l = 0; l < L; ++l) {
+            b->n_max = std::max<int>(b->n_max, b->info[l].n);
+            b->rot_max = std::max<int>(b->rot_max, b->info[l].nrot);
+        }
         GridDesc* h_grids = reinterpret_cast<GridDesc*>(hb + o_grids);
         for (size_t sl = 0; sl < pk.size(); ++sl) {
             h_grids[sl] = pk[sl]->desc;
@@ -768,61 +838,55 @@ void fill_desc(exs_pose_desc& d, float score, double s64, int k, int32_t tau_pac
 
 namespace {
 
-// The launch sequence of one job on `st`: a counter reset and one persistent dock
-// launch, or one dock launch per pocket group.
+// One dock launch of a job: its shape, and the ligands order[start .. start + count).
+struct DockLaunch {
+    DockShape shape;
+    int storage = 0, start = 0, count = 0, blocks = 0;
+};
+
+// The launch sequence of one job on `st`: a reset of the counters (queues, finished parts) where
+// one is read, then one persistent dock launch, or one dock launch per pocket group.
 // ev_dock / ev_rank (may be null): recorded on `st` after the search and after the ranking, so
 // that an eager job can report each kernel's time (never inside a graph capture).
-hipError_t enqueue_dock(const DockArgs& base, const Batch& b, const std::vector<int>& groups,
-                        const int32_t* d_order, int n_queues, int storage, int ppl, bool persistent,
-                        int resident, int threads, size_t lds, hipStream_t st,
+hipError_t enqueue_dock(const DockArgs& base, const Batch& b, const std::vector<DockLaunch>& launches,
+                        const int32_t* d_order, int n_queues, bool persistent, hipStream_t st,
                         hipEvent_t ev_dock = nullptr, hipEvent_t ev_rank = nullptr) {
     if (b.L == 0) return hipSuccess;
-    if (persistent) {
-        DockArgs a = base;
-        a.order = d_order;
-        a.n_order = b.L;
-        a.n_tiles = (b.L + a.lpw - 1) / a.lpw;
-        a.persistent = 1;
-        a.queue_bounds = d_order + b.L;
-        a.n_queues = n_queues;
-        hipError_t e = launch_zero_ints(a.tile_counter, n_queues, st);
+    bool parts = false;
+    for (const DockLaunch& d : launches) parts = parts || d.shape.parts > 1;
+    hipError_t e = hipSuccess;
+    if (persistent || parts) e = launch_zero_ints(base.tile_counter, kMaxWorkQueues + (parts ? b.L : 0), st);
+    for (const DockLaunch& d : launches) {
         if (e != hipSuccess) return e;
-        e = launch_dock(a, storage, ppl, resident, threads, lds, st);
-        if (e == hipSuccess && ev_dock) e = hipEventRecord(ev_dock, st);
-        if (e == hipSuccess && a.rank_keep > 0) e = launch_rank(a, b.L, d_order, st);
-        if (e == hipSuccess && ev_rank) e = hipEventRecord(ev_rank, st);
-        if (e == hipSuccess && a.rescore2) e = launch_rescore2(a, b.L, d_order, st);
-        return e;
-    }
-    int start = 0;
-    for (size_t gi = 0; gi < groups.size(); ++gi) {
-        const int gsz = groups[gi];
-        if (gsz == 0) continue;
         DockArgs a = base;
-        a.order = d_order + start;
-        a.n_order = gsz;
-        a.n_tiles = (gsz + a.lpw - 1) / a.lpw;
-        a.persistent = 0;
-        hipError_t e = launch_dock(a, b.storage_of_slot[gi], ppl, a.n_tiles, threads, lds, st);
-        if (e != hipSuccess) return e;
-        start += gsz;
+        a.order = d_order + d.start;
+        a.done = base.done + d.start;
+        a.n_order = d.count;
+        a.lds = d.shape.lds;
+        a.parts = d.shape.parts;
+        a.slot_floats = d.shape.slot_floats(a.lpw, a.n_max);
+        a.n_tiles = (d.count + a.lpw - 1) / a.lpw * a.parts;
+        a.persistent = persistent ? 1 : 0;
+        if (persistent) {
+            a.queue_bounds = d_order + b.L;
+            a.n_queues = n_queues;
+        }
+        e = launch_dock(a, d.storage, d.shape, d.blocks, st);
     }
-    hipError_t e = ev_dock ? hipEventRecord(ev_dock, st) : hipSuccess;
-    // d_order: every pocket's ligands, longest first, one pocket after another
+    if (e == hipSuccess && ev_dock) e = hipEventRecord(ev_dock, st);
+    // d_order: every pocket's ligands (or every queue's), longest first, one after another
     if (e == hipSuccess && base.rank_keep > 0) e = launch_rank(base, b.L, d_order, st);
     if (e == hipSuccess && ev_rank) e = hipEventRecord(ev_rank, st);
     if (e == hipSuccess && base.rescore2) e = launch_rescore2(base, b.L, d_order, st);
     return e;
 }
 
-// Validated search settings of a batch and the launch shape they give.
-struct LaunchShape {
-    int ppl = 1, wpl = 1, lpw = 1, threads = 64, top_k = 0, storage = 0;
-    size_t lds = 0;
-    const void* fn = nullptr;
+// Validated search settings of a batch.
+struct LaunchSettings {
+    int ppl = 1, lpw = 1, top_k = 0, storage = 0;
 };
 
-int launch_shape(const Batch& b, const exs_search_params& p, bool persistent, LaunchShape* out) {
+int launch_settings(const Batch& b, const exs_search_params& p, bool persistent, LaunchSettings* out) {
     if (p.n_orient < 1 || p.n_orient > EXS_MAX_ORIENT)
         return fail(EXS_EINVAL, "n_orient %d outside [1, %d]", p.n_orient, EXS_MAX_ORIENT);
     if (p.torsion_steps != 8 && p.torsion_steps != 16 && p.torsion_steps != 32)
@@ -840,22 +904,14 @@ int launch_shape(const Batch& b, const exs_search_params& p, bool persistent, La
         return fail(EXS_EINVAL, "cluster_rmsd_A must be finite and >= 0");
     if ((p.flags & EXS_FLAG_RESCORE2) && p.rank_keep <= 0)
         return fail(EXS_EINVAL, "EXS_FLAG_RESCORE2 rescores the ranked poses: it needs rank_keep > 0");
-    LaunchShape& sh = *out;
-    sh.ppl = p.poses_per_lane ? p.poses_per_lane : 1;
-    if (sh.ppl != 1 && sh.ppl != 2 && sh.ppl != 4)
-        return fail(EXS_EINVAL, "poses_per_lane %d: supported 1, 2, 4", sh.ppl);
-    const int K = p.n_orient;
-    sh.wpl = (K + kWave * sh.ppl - 1) / (kWave * sh.ppl);
-    sh.lpw = p.ligands_per_wg;
-    if (sh.lpw == 0) sh.lpw = std::max(1, std::min(kMaxLpw, kMaxWavesPerWg / std::max(1, sh.wpl) / 2));
-    if (sh.lpw != 1 && sh.lpw != 2 && sh.lpw != 4 && sh.lpw != 8)
-        return fail(EXS_EINVAL, "ligands_per_wg %d: supported 1, 2, 4, 8", sh.lpw);
-    sh.top_k = std::min(p.top_k, K);
-    const int waves = dock_waves(sh.lpw, sh.wpl, sh.top_k, sh.ppl, p.torsion_steps);
-    if (waves < 1)
-        return fail(EXS_EINVAL, "tile of %d ligands x %d poses per lane does not fit in %zu B of LDS",
-                    sh.lpw, sh.ppl, kMaxLdsBytes);
-    sh.threads = waves * kWave;
+    LaunchSettings& ls = *out;
+    ls.ppl = p.poses_per_lane ? p.poses_per_lane : 1;
+    if (ls.ppl != 1 && ls.ppl != 2 && ls.ppl != 4)
+        return fail(EXS_EINVAL, "poses_per_lane %d: supported 1, 2, 4", ls.ppl);
+    ls.lpw = p.ligands_per_wg ? p.ligands_per_wg : 1;
+    if (ls.lpw != 1 && ls.lpw != 2 && ls.lpw != 4 && ls.lpw != 8)
+        return fail(EXS_EINVAL, "ligands_per_wg %d: supported 1, 2, 4, 8", ls.lpw);
+    ls.top_k = std::min(p.top_k, p.n_orient);
     int storage = -1;
     for (size_t s = 0; s < b.pockets.size(); ++s) {
         auto pk = find_pocket(b.pockets[s]);
@@ -864,48 +920,47 @@ int launch_shape(const Batch& b, const exs_search_params& p, bool persistent, La
             return fail(EXS_EINVAL, "persistent launch needs one texel storage for all pockets");
         storage = storage < 0 ? pk->storage : storage;
     }
-    sh.storage = storage < 0 ? 0 : storage;
-    sh.lds = dock_lds_bytes(sh.lpw, sh.top_k, waves, sh.ppl, p.torsion_steps);
-    sh.fn = dock_kernel_fn(sh.storage, p.torsion_steps, sh.ppl);
-    if (!sh.fn) return fail(EXS_EINVAL, "no kernel for this configuration");
-    if (sh.lds > 64 * 1024) {
-        hipError_t e = hipFuncSetAttribute(sh.fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)sh.lds);
-        if (e != hipSuccess) return fail(EXS_EDEVICE, "LDS %zu: %s", sh.lds, hipGetErrorString(e));
-    }
+    ls.storage = storage < 0 ? 0 : storage;
     return EXS_OK;
 }
 
 // Launch arguments of batch b under settings p (batch, pocket and search fields); outputs,
-// scratch and the processing order are left null.
-void base_args(DockArgs& a, const Batch& b, const exs_search_params& p, const LaunchShape& sh,
-               const float* r32, const double* r64) {
+// scratch, launch shape and the processing order are left null.
+void base_args(DockArgs& a, const Batch& b, const exs_search_params& p, const LaunchSettings& ls,
+               const float* r32, const double* r64, const int32_t* order_k) {
     memset(&a, 0, sizeof a);
     a.info = b.d_info; a.ref = b.d_ref; a.ref64 = b.d_ref64; a.excl = b.d_excl;
     a.rot_uv = b.d_rot_uv; a.rot_mask = b.d_rot_mask; a.grids = b.d_grids;
-    a.rot32 = r32; a.rot64 = r64;
+    a.rot32 = r32; a.rot64 = r64; a.order_k = order_k;
     a.K = p.n_orient; a.S = p.torsion_steps; a.P = p.passes; a.T = p.n_offsets;
     a.step = p.offset_step_A; a.cut2 = p.clash_cutoff_A * p.clash_cutoff_A; a.pen = p.clash_penalty;
     a.step64 = (double)p.offset_step_A;
     a.cut2_64 = (double)p.clash_cutoff_A * (double)p.clash_cutoff_A;
     a.pen64 = (double)p.clash_penalty;
-    a.top_k = sh.top_k; a.lpw = sh.lpw; a.wpl = sh.wpl; a.kp = sh.wpl * kWave * sh.ppl;
+    a.top_k = ls.top_k; a.lpw = ls.lpw;
     a.rank_keep = p.rank_keep;
     a.rank_thr2 = p.cluster_rmsd_A * p.cluster_rmsd_A;
     a.n_max = b.n_max;
-    a.slot_floats = (int64_t)sh.lpw * a.n_max * 3 * a.kp;
     a.rescore2 = (p.flags & EXS_FLAG_RESCORE2) ? 1 : 0;
     a.rot_ac = b.d_rot_ac;
     a.eps2 = EXS_RESCORE2_CONTACT_EPS;
     a.w2 = EXS_RESCORE2_TORSION_W;
 }
 
-// Workgroups of a persistent launch of shape sh that are resident at once on device dev.
-int resident_workgroups(int dev, const LaunchShape& sh) {
-    int per_cu = 0;
-    hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, sh.fn, sh.threads, sh.lds);
-    if (e != hipSuccess || per_cu < 1) per_cu = 1;
-    std::lock_guard<std::mutex> lk(g_dev_mu);
-    return per_cu * std::max(1, g_dev[dev].cus);
+// The launch of `count` ligands of batch b, from position `start` of the order.
+int plan_launch(const Batch& b, const exs_search_params& p, const LaunchSettings& ls, int dev, int storage,
+                int start, int count, bool persistent, DockLaunch* out) {
+    out->shape = dock_shape(count, b.n_max, b.rot_max, p.n_orient, p.torsion_steps, ls.top_k, ls.lpw, ls.ppl,
+                            rt::device_cus(dev));
+    out->storage = storage;
+    out->start = start;
+    out->count = count;
+    out->blocks = (count + ls.lpw - 1) / ls.lpw * out->shape.parts;
+    int resident = 0;
+    if (int rc = rt::resident_workgroups(dev, storage, p.torsion_steps, out->shape, &resident)) return rc;
+    // parts share scratch slots by tile, so every tile has a slot and is launched
+    if (persistent && out->shape.parts == 1) out->blocks = std::max(1, std::min(out->blocks, resident));
+    return EXS_OK;
 }
 
 }  // namespace
@@ -919,11 +974,9 @@ int exs_dock_batch(int64_t batch, const exs_search_params* params, void* stream,
         if (!b) return fail(EXS_ENOENT, "unknown batch %lld", (long long)batch);
         const exs_search_params& p = *params;
         const bool persistent = (p.flags & EXS_FLAG_PERSISTENT) != 0;
-        LaunchShape sh;
-        if (int rc = launch_shape(*b, p, persistent, &sh)) return rc;
-        const int ppl = sh.ppl, lpw = sh.lpw, threads = sh.threads, top_k = sh.top_k;
-        const int storage = sh.storage;
-        const size_t lds = sh.lds;
+        LaunchSettings ls;
+        if (int rc = launch_settings(*b, p, persistent, &ls)) return rc;
+        const int ppl = ls.ppl, lpw = ls.lpw, top_k = ls.top_k;
         const int K = p.n_orient;
         int dev;
         if (int rc = current_device(&dev)) return rc;
@@ -931,7 +984,8 @@ int exs_dock_batch(int64_t batch, const exs_search_params* params, void* stream,
         hipStream_t st = (hipStream_t)stream;
         const float* r32;
         const double* r64;
-        if (int rc = orientation_tables(dev, K, &r32, &r64)) return rc;
+        const int32_t* order_k;
+        if (int rc = orientation_tables(dev, K, &r32, &r64, &order_k)) return rc;
         int32_t* d_order = nullptr;
         std::vector<int> groups;
         int n_queues = 1;
@@ -942,15 +996,16 @@ int exs_dock_batch(int64_t batch, const exs_search_params* params, void* stream,
         j->device = dev; j->batch = b; j->prm = p; j->stream = st;
         j->L = b->L; j->A = b->A; j->R = b->R; j->K = K; j->top_k = top_k;
         const int L = b->L;
-        // workgroup slots of pose scratch: resident workgroups (persistent) or the largest launch
-        int64_t slots = 0;
-        int resident = 0;
-        if (persistent) {
-            const int n_tiles = (L + lpw - 1) / lpw;
-            resident = std::max(1, std::min(n_tiles, resident_workgroups(dev, sh)));
-            slots = resident;
-        } else {
-            for (int gsz : groups) slots = std::max<int64_t>(slots, (gsz + lpw - 1) / lpw);
+        // the launches, and the floats of pose scratch that the largest of them needs
+        std::vector<DockLaunch> launches;
+        int64_t scratch_floats = 1;
+        for (int gi = 0, start = 0; gi < (int)groups.size(); start += groups[gi], ++gi) {
+            if (groups[gi] == 0) continue;
+            DockLaunch d;
+            if (int rc = plan_launch(*b, p, ls, dev, persistent ? ls.storage : b->storage_of_slot[gi], start,
+                                     groups[gi], persistent, &d)) return rc;
+            scratch_floats = std::max(scratch_floats, d.blocks * d.shape.slot_floats(lpw, b->n_max));
+            launches.push_back(d);
         }
         const bool graph = (p.flags & EXS_FLAG_GRAPH) != 0;
         std::shared_ptr<Plan> plan;
@@ -975,7 +1030,7 @@ int exs_dock_batch(int64_t batch, const exs_search_params* params, void* stream,
             j->args = plan->args;
         } else {
             DockArgs& a = j->args;
-            base_args(a, *b, p, sh, r32, r64);
+            base_args(a, *b, p, ls, r32, r64, order_k);
             std::shared_ptr<Plan> fresh;
             if (graph) fresh = std::make_shared<Plan>();
             Alloc al{graph ? &fresh->bufs : &j->bufs, st, !graph};
@@ -1001,11 +1056,12 @@ int exs_dock_batch(int64_t batch, const exs_search_params* params, void* stream,
                 (rc = job_alloc(al, &a.score2, a.rescore2 ? (size_t)L * p.rank_keep : (size_t)0)) ||
                 (rc = job_alloc(al, &a.best2_k, a.rescore2 ? (size_t)L : (size_t)0)) ||
                 (rc = job_alloc(al, &a.best2, a.rescore2 ? (size_t)L : (size_t)0)) ||
-                (rc = job_alloc(al, &a.tile_counter, (size_t)kMaxWorkQueues)) ||
-                (rc = job_alloc(al, &a.scratch, (size_t)std::max<int64_t>(slots, 1) * a.slot_floats))) {
+                (rc = job_alloc(al, &a.tile_counter, (size_t)kMaxWorkQueues + L)) ||
+                (rc = job_alloc(al, &a.scratch, (size_t)scratch_floats))) {
                 free_allocs(al);
                 return rc;
             }
+            a.done = a.tile_counter + kMaxWorkQueues;
             if (graph) {
                 fresh->args = a;
                 // capture the launch sequence once on a private stream
@@ -1013,8 +1069,7 @@ int exs_dock_batch(int64_t batch, const exs_search_params* params, void* stream,
                 HIP_TRY(hipStreamCreateWithFlags(&cs, hipStreamNonBlocking));
                 hipError_t e = hipStreamBeginCapture(cs, hipStreamCaptureModeThreadLocal);
                 if (e == hipSuccess) {
-                    e = enqueue_dock(a, *b, groups, d_order, n_queues, storage, ppl, persistent,
-                                     resident, threads, lds, cs);
+                    e = enqueue_dock(a, *b, launches, d_order, n_queues, persistent, cs);
                     hipGraph_t gr = nullptr;
                     hipError_t e2 = hipStreamEndCapture(cs, &gr);
                     if (e == hipSuccess) e = e2;
@@ -1046,8 +1101,8 @@ int exs_dock_batch(int64_t batch, const exs_search_params* params, void* stream,
         if (j->plan) {
             HIP_TRY(hipGraphLaunch(j->plan->exec, st));
         } else {
-            HIP_TRY(enqueue_dock(j->args, *b, groups, d_order, n_queues, storage, ppl, persistent,
-                                 resident, threads, lds, st, j->ev_dock, j->ev_rank));
+            HIP_TRY(enqueue_dock(j->args, *b, launches, d_order, n_queues, persistent, st, j->ev_dock,
+                                 j->ev_rank));
         }
         HIP_TRY(hipEventRecord(j->ev1, st));
         std::lock_guard<std::mutex> lk(g_reg_mu);
@@ -1348,22 +1403,29 @@ int noalloc_plan(int64_t batch, const exs_search_params* params, NoAllocPlan* ou
     int dev;
     if (int rc = current_device(&dev)) return rc;
     if (dev != b->device) return fail(EXS_EINVAL, "batch lives on device %d, current is %d", b->device, dev);
-    LaunchShape sh;
-    if (int rc = launch_shape(*b, p, true, &sh)) return rc;
-    base_args(out->args, *b, p, sh, nullptr, nullptr);
+    LaunchSettings ls;
+    if (int rc = launch_settings(*b, p, true, &ls)) return rc;
+    base_args(out->args, *b, p, ls, nullptr, nullptr, nullptr);
+    DockLaunch d;
+    if (b->L > 0)
+        if (int rc = plan_launch(*b, p, ls, dev, ls.storage, 0, b->L, true, &d)) return rc;
     DockArgs& a = out->args;
     a.order = b->d_upload_order;
     a.n_order = b->L;
-    a.n_tiles = (b->L + sh.lpw - 1) / sh.lpw;
+    a.lds = d.shape.lds;
+    a.parts = d.shape.parts;
+    a.slot_floats = d.shape.slot_floats(a.lpw, a.n_max);
+    a.n_tiles = (b->L + a.lpw - 1) / a.lpw * a.parts;
     a.persistent = 1;
     a.queue_bounds = nullptr;
     a.n_queues = 1;
     out->device = dev;
-    out->storage = sh.storage;
-    out->ppl = sh.ppl;
-    out->threads = sh.threads;
-    out->lds = sh.lds;
-    out->resident = resident_workgroups(dev, sh);
+    out->storage = ls.storage;
+    out->shape = d.shape;
+    out->blocks = d.blocks;
+    // what the buffer's limit counts for a workgroup: a pose per orientation, in groups of 64
+    const int64_t group = kWave * ls.ppl;
+    out->limit_bytes = (int64_t)sizeof(float) * ls.lpw * b->n_max * 3 * ((a.K + group - 1) / group * group);
     out->L = b->L; out->A = b->A; out->R = b->R;
     return EXS_OK;
 }

@@ -87,9 +87,8 @@ static_assert(sizeof(LigInfo) == 32, "LigInfo layout");
 
 // One pocket as the kernels see it.
 struct GridDesc {
-    const void* tex;       // per-cell gather blocks, one channel every chan_bytes: the 8 corners
-                           // of a cell, 32 B in FP32 (x pairs as a, b - a, cells x fastest),
-                           // 16 B in BF16/FP16 (cells in 2 x 2 x 2 bricks of one line)
+    const void* tex;       // gather layout, one channel every chan_bytes: per node the four texels
+                           // of its y-z square, 16 B in FP32, 8 B in BF16/FP16, x fastest
     const float* master;   // FP32 master texels [C][nz][ny][nx] (FP64 rescoring)
     int nx, ny, nz, channels;
     float ox, oy, oz, inv_h;   // origin and 1/spacing, FP32
@@ -103,7 +102,6 @@ struct GridDesc {
     int32_t pad3;
 };
 
-// Everything one dock launch reads and writes.
 // Serving: the results of one iteration's ligands in contiguous host memory (one record per
 // ligand, then coordinates and torsion bytes at host-computed offsets).
 struct ResultRec {
@@ -114,6 +112,60 @@ struct ResultRec {
     double score64;
 };
 
+// Dynamic LDS of a dock workgroup (byte offsets): the turn table, per ligand of the tile its
+// topology (ref .. topk relative to the ligand's slot), the waves' best (score, orientation) per
+// ligand, and per wave its poses, clash difference arrays, queue of crossing pairs and torsions
+// (diff, queue, theta relative to the wave's part).  Sized by the launch's largest ligand: LDS decides how many waves fit on a CU.
+struct DockLds {
+    int32_t ligs, lig_bytes;
+    int32_t ref, excl, rmask, ruv, mc, perm, perm_stride, e64, topk;
+    int32_t rec;
+    int32_t waves, wave_bytes, diff, queue, theta;
+    int32_t total;
+};
+__host__ __device__ inline int lds_align(int x) { return (x + 15) & ~15; }
+inline DockLds dock_lds(int lpw, int n_max, int rot_max, int top_k, int waves, int lanes, int S) {
+    DockLds d;
+    const int no = kWave / lanes;
+    int at = lds_align(2 * S * 4);
+    d.ligs = at;
+    int p = 32;                                   // lig, n, nrot, pocket, atom_base, rot_base
+    d.ref = p; p += 16 * n_max;
+    d.excl = p; p += 16 * n_max;
+    d.rmask = p; p += 16 * rot_max;
+    d.e64 = p; p += lds_align(8 * top_k);
+    d.topk = p; p += lds_align(4 * top_k);
+    d.ruv = p; p += lds_align(4 * rot_max);
+    d.mc = p; p += lds_align(4 * rot_max);
+    d.perm = p;
+    d.perm_stride = (n_max + 3) & ~3;
+    p += lds_align(d.perm_stride * rot_max);
+    d.lig_bytes = p;
+    at += lpw * d.lig_bytes;
+    d.rec = at; at += lds_align(8 * lpw * waves);
+    d.waves = at;
+    p = lds_align(12 * n_max * no);               // the poses (the FP64 ones of the top_k, 24 n_max, fit)
+    d.diff = p; p += lds_align(2 * S * no);
+    d.queue = p; p += 13 * kWave;
+    d.theta = p; p += lds_align(rot_max * no);
+    d.wave_bytes = p;
+    d.total = at + waves * d.wave_bytes;
+    return d;
+}
+constexpr size_t kMaxLdsBytes = 160 * 1024;   // gfx950 LDS per workgroup
+constexpr int kDockLdsBytes = (int)kMaxLdsBytes - 256;   // dynamic LDS beside the dock kernel's static words
+// Floats in front of a scratch slot's poses: the part's best score, orientation and wave.
+constexpr int kSlotHead = 4;
+
+// Shape of a dock launch: lanes per orientation, waves of a workgroup, workgroups per ligand.
+struct DockShape {
+    int lanes = 4, waves = 1, parts = 1;
+    DockLds lds{};
+    int64_t slot_floats(int lpw, int n_max) const { return kSlotHead + (int64_t)lpw * waves * 3 * n_max; }
+};
+DockShape dock_shape(int n_lig, int n_max, int rot_max, int K, int S, int top_k, int lpw, int ppl, int cus);
+
+// Everything one dock launch reads and writes.
 struct DockArgs {
     // packed ligand batch
     const LigInfo* info;
@@ -124,25 +176,28 @@ struct DockArgs {
     const uint4* rot_mask;    // [R] atoms that turn with the bond
     const int32_t* order;     // ligands in processing order (pocket-major, longest first within)
     int32_t n_order;          // ligands in this launch
-    int32_t n_tiles;          // ceil(n_order / lpw)
+    int32_t n_tiles;          // workgroups' worth of work: ceil(n_order / lpw), times parts
     // pockets
     const GridDesc* grids;
     // search settings
     const float* rot32;       // [K][9] orientation matrices, row-major
     const double* rot64;      // [K][9]
+    const int32_t* order_k;   // [K] the orientations in the order the chunks take them
     int32_t K, S, P, T;
     float step, cut2, pen, pad0;
     double step64, cut2_64, pen64;
     int32_t top_k;
     int32_t lpw;              // ligands per workgroup
-    int32_t wpl;              // waves per ligand = ceil(K / (64 * ppl))
-    int32_t kp;               // padded orientations per ligand = wpl * 64 * ppl
+    int32_t parts;            // workgroups that share a ligand's chunks (> 1: lpw = 1)
     int32_t n_max;            // atoms of the largest ligand in the launch
     int32_t persistent;
-    // per-workgroup-slot scratch of pose coordinates: [lpw][n_max][3][kp] floats
+    DockLds lds;
+    // scratch slots, one per workgroup (parts > 1: one per tile): a record of kSlotHead floats,
+    // then [lpw][waves][n_max][3]
     float* scratch;
     int64_t slot_floats;
     int32_t* tile_counter;    // persistent launches: next tile of each queue [n_queues]
+    int32_t* done;            // parts > 1: finished parts of each position of `order`, zeroed
     // persistent launches: n_queues + 1 positions in `order`, queue q = [qb[q], qb[q+1]);
     // a workgroup takes tiles from queue (its XCD index mod n_queues) first, then from the
     // others.  Null, or n_queues = 1: one queue over the whole order.
@@ -197,7 +252,7 @@ __host__ __device__ inline int rank_lds_words(int K, int n_max) {
     return 4 * K + (K + 31) / 32 + 8 * 3 * n_max;
 }
 
-// Per-ligand LDS staging of a tile (topology read wave-uniformly by the search).
+// A ligand's topology in the LDS of the second-stage rescoring.
 struct LigLds {
     float4 ref[kMaxAtoms];     // centred reference coordinates, type in .w
     uint4 excl[kMaxAtoms];     // exclusion rows
@@ -205,35 +260,12 @@ struct LigLds {
     uint32_t ruv[kMaxRot];     // u | v << 16
     int32_t lig, n, nrot, pocket;
     int32_t atom_base, rot_base, pad0, pad1;
-    int32_t topk[kMaxTopK];
 };
 
-// Dynamic LDS bytes of a dock launch: the tile's ligands, the FP64 rescoring poses (top_k > 0)
-// and, per wave, a clash difference array of S counters per pose slot and lane.
-__host__ __device__ inline size_t dock_lds_x64_offset(int lpw) { return (size_t)lpw * sizeof(LigLds); }
-__host__ __device__ inline size_t dock_lds_diff_offset(int lpw, int top_k) {
-    return dock_lds_x64_offset(lpw) + (top_k > 0 ? (size_t)lpw * kMaxAtoms * 3 * sizeof(double) : 0);
-}
-__host__ __device__ inline size_t dock_lds_bytes(int lpw, int top_k, int waves, int ppl, int S) {
-    return dock_lds_diff_offset(lpw, top_k) + (size_t)waves * ppl * S * kWave * sizeof(int32_t);
-}
-constexpr size_t kMaxLdsBytes = 160 * 1024;   // gfx950 LDS per workgroup
-// Waves of a dock workgroup for a tile of lpw ligands x wpl orientation chunks: one per chunk
-// up to kMaxWavesPerWg, fewer if their clash difference arrays would not fit in LDS (the waves
-// then take the chunks in turn); 0 if not even one wave fits.
-__host__ __device__ inline int dock_waves(int lpw, int wpl, int top_k, int ppl, int S) {
-    int w = lpw * wpl < kMaxWavesPerWg ? lpw * wpl : kMaxWavesPerWg;
-    while (w > 0 && dock_lds_bytes(lpw, top_k, w, ppl, S) > kMaxLdsBytes) --w;
-    return w;
-}
-
 // Launchers (dock_misc.hip).
-hipError_t launch_dock(const DockArgs& a, int storage, int ppl, int n_blocks, int threads,
-                       size_t lds, hipStream_t st);
-// Per-cell gather layout of a pocket channel, in 16-byte entries: the 8 corners of each of the
-// (nx-1)(ny-1)(nz-1) cells, two entries per cell for FP32; one per cell for 16-bit, in
-// 2 x 2 x 2 bricks (8 * (nx/2)(ny/2)(nz/2) entries with the padding of odd edges).
-int64_t expanded_entries(int nx, int ny, int nz, int storage);
+hipError_t launch_dock(const DockArgs& a, int storage, const DockShape& sh, int n_blocks, hipStream_t st);
+// Bytes of a pocket channel's gather layout: nx (ny-1)(nz-1) entries of four texels.
+int64_t expanded_bytes(int nx, int ny, int nz, int storage);
 hipError_t launch_expand_grid(const float* src, void* dst, int nx, int ny, int nz, int channels,
                               int storage, hipStream_t st);
 // Gather probe over the pocket `gd` (device pointer) in `storage`: blocks x 256 lanes, nb
@@ -259,9 +291,10 @@ hipError_t launch_stage_ints(const int32_t* src, int32_t* dst, int n, int* zero,
                              int n_lig, int32_t* slot, hipStream_t st);
 // *flag |= 1 if a texel is not finite, |= 2 if one overflows the 16-bit storage (storage 1, 2).
 hipError_t launch_check_texels(const float* v, int64_t count, int storage, int* flag, hipStream_t st);
-// K orientation matrices [K][9] (row-major), FP32 and (unless r64 is null) FP64.
-hipError_t launch_orientation_table(int K, float* r32, double* r64, hipStream_t st);
+// K orientation matrices [K][9] (row-major), FP32 and (unless r64 is null) FP64, and the order in
+// which the chunks take the orientations [K].
+hipError_t launch_orientation_table(int K, float* r32, double* r64, int32_t* order_k, hipStream_t st);
 hipError_t upload_trig_tables();
-const void* dock_kernel_fn(int storage, int S, int ppl);
+const void* dock_kernel_fn(int storage, int S, int lanes);
 
 }  // namespace exs

@@ -80,15 +80,23 @@ extern "C" int exs_dock_batch_noalloc(int64_t batch, const exs_search_params* pa
     a.orient_score = c.take<float>((size_t)L * K);
     a.orient_tau = c.take<int32_t>((size_t)L * K);
     a.orient_theta = c.take<uint8_t>((size_t)R * K);
-    const size_t slot_bytes = (size_t)a.slot_floats * sizeof(float);
-    if (c.used + slot_bytes > kScratchBytes)
+    if (c.used + (size_t)pl.limit_bytes > kScratchBytes)
         return rt::fail(EXS_EINVAL,
                         "batch needs %zu B of per-orientation results and %zu B per workgroup of "
                         "pose scratch; the no-allocation buffer holds %zu B (split the batch)",
-                        c.used, slot_bytes, kScratchBytes);
-    const int64_t fit = (int64_t)((kScratchBytes - c.used) / slot_bytes);
-    const int blocks = (int)std::max<int64_t>(1, std::min<int64_t>({(int64_t)pl.resident,
-                                                                    (int64_t)a.n_tiles, fit}));
+                        c.used, (size_t)pl.limit_bytes, kScratchBytes);
+    // the rest takes less than limit_bytes for one workgroup: the order of the orientations, the
+    // finished-part counters (a launch that splits its ligands) and the scratch slots
+    int32_t* order_k = c.take<int32_t>((size_t)K);
+    a.order_k = order_k;
+    const size_t slot_bytes = (size_t)a.slot_floats * sizeof(float);
+    if (a.parts > 1) a.done = c.take<int32_t>((size_t)L);
+    const int64_t fit = std::max<int64_t>(0, (int64_t)kScratchBytes - (int64_t)c.used) / (int64_t)slot_bytes;
+    if (a.parts > 1 && fit < pl.blocks) {   // a slot per tile does not fit: whole ligands, a slot per workgroup
+        a.parts = 1;
+        a.n_tiles = (int)((L + a.lpw - 1) / a.lpw);
+    }
+    const int blocks = (int)std::max<int64_t>(1, std::min<int64_t>(pl.blocks, fit));
     a.scratch = c.take<float>((size_t)blocks * a.slot_floats);
     a.best_score = best_score;
     a.best_k = best_orient;
@@ -96,9 +104,10 @@ extern "C" int exs_dock_batch_noalloc(int64_t batch, const exs_search_params* pa
     a.best_theta = best_theta;
     a.best_coords = best_coords;
     hipStream_t st = static_cast<hipStream_t>(stream);
-    hipError_t e = launch_orientation_table((int)K, rot32, nullptr, st);
+    hipError_t e = launch_orientation_table((int)K, rot32, nullptr, order_k, st);
     if (e == hipSuccess) e = launch_zero_ints(a.tile_counter, kMaxWorkQueues, st);
-    if (e == hipSuccess) e = launch_dock(a, pl.storage, pl.ppl, blocks, pl.threads, pl.lds, st);
+    if (e == hipSuccess && a.parts > 1) e = launch_zero_ints(a.done, (int)L, st);
+    if (e == hipSuccess) e = launch_dock(a, pl.storage, pl.shape, blocks, st);
     if (e != hipSuccess) return rt::fail(EXS_EDEVICE, "no-allocation launch: %s", hipGetErrorString(e));
     return EXS_OK;
 }

@@ -115,6 +115,17 @@ hipError_t own_queue_stream(int cus, hipStream_t* s) {
     return hipStreamCreateWithFlags(s, hipStreamNonBlocking);
 }
 
+// Workgroups whose pose scratch (a pose per orientation) the budget sets aside per iteration, and
+// of which four waves make the default iteration: the part of a budget that is not for requests,
+// as callers size their budgets by it.
+int accounted_workgroups(int cus, int lpw, int wpl, int ppl, int top_k, int S) {
+    const int lig = lpw * (4896 + (top_k > 0 ? 24 * EXS_MAX_ATOMS : 0)), wave = ppl * S * 256;
+    int waves = std::min(lpw * wpl, kMaxWavesPerWg);
+    while (waves > 1 && lig + waves * wave > (int)kMaxLdsBytes) --waves;
+    const int by_lds = (int)kMaxLdsBytes / (lig + waves * wave), by_waves = (ppl == 1 ? 12 : (ppl == 2 ? 8 : 4)) / waves;
+    return std::max(1, cus) * std::max(1, std::min(by_lds, by_waves));
+}
+
 struct Request {
     int64_t id = 0;
     int L = 0, A = 0, R = 0;
@@ -182,10 +193,10 @@ class Server {
 
     int dev_ = 0;
     exs_search_params prm_{};
-    int K_ = 0, ppl_ = 1, lpw_ = 1, wpl_ = 1, threads_ = 64, top_k_ = 0, storage_ = 0;
-    int resident_ = 1, max_iter_ = 0, n_iters_ = 2;
+    int K_ = 0, ppl_ = 1, lpw_ = 1, wpl_ = 1, top_k_ = 0, storage_ = 0;
+    int max_iter_ = 0, n_iters_ = 2;
+    int64_t scratch_floats_ = 0;   // of one iteration
     size_t res_rec_bytes_ = 0, res_coord_bytes_ = 0, res_theta_bytes_ = 0;   // staging regions
-    size_t lds_ = 0;
     std::vector<int32_t> pocket_ids_;
     std::unordered_map<int32_t, int> pocket_slot_;
     std::vector<int> channels_;
@@ -245,10 +256,6 @@ int Server::create(const int32_t* pockets, int n_pockets, const exs_search_param
     if (lpw_ != 1 && lpw_ != 2 && lpw_ != 4 && lpw_ != 8)
         return rt::fail(EXS_EINVAL, "ligands_per_wg %d: supported 1, 2, 4, 8", lpw_);
     top_k_ = std::min(p.top_k, K_);
-    const int waves = dock_waves(lpw_, wpl_, top_k_, ppl_, p.torsion_steps);
-    if (waves < 1) return rt::fail(EXS_EINVAL, "tile does not fit in LDS");
-    threads_ = waves * kWave;
-    lds_ = dock_lds_bytes(lpw_, top_k_, waves, ppl_, p.torsion_steps);
     n_iters_ = cfg.max_inflight_iters == 1 ? 1 : 2;
     // pockets
     std::vector<GridDesc> grids;
@@ -263,23 +270,20 @@ int Server::create(const int32_t* pockets, int n_pockets, const exs_search_param
         channels_.push_back(pi.channels);
         grids.push_back(pi.desc);
     }
-    const void* fn = dock_kernel_fn(storage_, p.torsion_steps, ppl_);
-    if (lds_ > 64 * 1024)
-        SRV_TRY(hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_));
-    int per_cu = 1;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, fn, threads_, lds_) != hipSuccess || per_cu < 1)
-        per_cu = 1;
-    resident_ = std::max(1, per_cu * rt::device_cus(dev_));
+    const int wgs = accounted_workgroups(rt::device_cus(dev_), lpw_, wpl_, ppl_, top_k_, p.torsion_steps);
     // default: four waves of workgroups' worth of ligands (with two iterations in flight, two
     // measured the same latency at 0.7 of capacity and a 25 % higher p99 at 0.9; one lost
     // throughput to the iterations' tails)
-    max_iter_ = cfg.max_iter_ligands > 0 ? cfg.max_iter_ligands : 4 * resident_ * lpw_;
+    max_iter_ = cfg.max_iter_ligands > 0 ? cfg.max_iter_ligands : 4 * wgs * lpw_;
     // budget: scratch for the iterations first, the rest is the request arena
     const int64_t slot_floats = (int64_t)lpw_ * EXS_MAX_ATOMS * 3 * (wpl_ * kWave * ppl_);
+    // what is allocated of it: the waves' best poses take a small part (64 MB hold 43,000 of the
+    // largest ligands'; a launch that splits its ligands further than that is not split)
+    scratch_floats_ = std::min<int64_t>(wgs * slot_floats, (int64_t)1 << 24);
     res_rec_bytes_ = sizeof(ResultRec) * (size_t)max_iter_;
     res_coord_bytes_ = sizeof(float) * 3 * (size_t)EXS_MAX_ATOMS * max_iter_;
     res_theta_bytes_ = (size_t)EXS_MAX_ROT * max_iter_;
-    const int64_t scratch_bytes = (int64_t)n_iters_ * resident_ * slot_floats * 4 +
+    const int64_t scratch_bytes = (int64_t)n_iters_ * wgs * slot_floats * 4 +
                                   (int64_t)n_iters_ * (4 * (int64_t)max_iter_ + kMaxWorkQueues + 1) * 4;
     per_lig_ = 32 + 12LL * K_ + 40 + 28LL * top_k_ + 4;   // info, per-orientation, best, top-k, order
     per_atom_ = 16 + 24 + 16 + 12;
@@ -339,14 +343,12 @@ int Server::create(const int32_t* pockets, int n_pockets, const exs_search_param
     SRV_TRY(hipMemcpy(dg, grids.data(), grids.size() * sizeof(GridDesc), hipMemcpyHostToDevice));
     a.info = info; a.ref = ref; a.ref64 = ref64; a.excl = excl; a.rot_uv = ruv; a.rot_mask = rmask;
     a.grids = dg;
-    if ((rc = rt::orientation_tables(dev_, K_, &a.rot32, &a.rot64))) return rc;
+    if ((rc = rt::orientation_tables(dev_, K_, &a.rot32, &a.rot64, &a.order_k))) return rc;
     a.K = K_; a.S = p.torsion_steps; a.P = p.passes; a.T = p.n_offsets;
     a.step = p.offset_step_A; a.cut2 = p.clash_cutoff_A * p.clash_cutoff_A; a.pen = p.clash_penalty;
     a.step64 = p.offset_step_A; a.cut2_64 = (double)p.clash_cutoff_A * p.clash_cutoff_A;
     a.pen64 = p.clash_penalty;
-    a.top_k = top_k_; a.lpw = lpw_; a.wpl = wpl_; a.kp = wpl_ * kWave * ppl_;
-    a.n_max = EXS_MAX_ATOMS;
-    a.slot_floats = slot_floats;
+    a.top_k = top_k_; a.lpw = lpw_;
     a.persistent = 1;
     // the streams get a hardware queue each, several ms apiece: created on threads of their own
     {
@@ -375,8 +377,8 @@ int Server::create(const int32_t* pockets, int n_pockets, const exs_search_param
         Iteration& it = it_[i];
         SRV_TRY(hipEventCreateWithFlags(&it.done, hipEventDisableTiming));
         if ((rc = dev_alloc(dev_bufs_, &it.d_order, 4 * (size_t)max_iter_ + kMaxWorkQueues + 1)) ||
-            (rc = dev_alloc(dev_bufs_, &it.d_counter, kMaxWorkQueues)) ||
-            (rc = dev_alloc(dev_bufs_, &it.scratch, (size_t)resident_ * slot_floats)))
+            (rc = dev_alloc(dev_bufs_, &it.d_counter, (size_t)kMaxWorkQueues + max_iter_)) ||
+            (rc = dev_alloc(dev_bufs_, &it.scratch, (size_t)scratch_floats_)))
             return rc;
         // mapped, coherent pinned memory: kernels read and write it over the bus, uncached
         SRV_TRY(hipHostMalloc((void**)&it.h_order, sizeof(int32_t) * (4 * (size_t)max_iter_ + kMaxWorkQueues + 1),
@@ -567,8 +569,26 @@ bool Server::launch(Iteration& it) {
     DockArgs a = base_;
     a.order = it.d_order;
     a.n_order = n;
-    a.n_tiles = (a.n_order + lpw_ - 1) / lpw_;
+    // the launch's shape from its own largest ligand
+    const int n_max = std::max(1, (int)*std::max_element(nat.begin(), nat.end()));
+    const int rot_max = *std::max_element(nrt.begin(), nrt.end());
+    DockShape sh = dock_shape(n, n_max, rot_max, K_, prm_.torsion_steps, top_k_, lpw_, ppl_, rt::device_cus(dev_));
+    if (sh.parts > 1 && (int64_t)n * sh.parts * sh.slot_floats(lpw_, n_max) > scratch_floats_)
+        sh.parts = 1;   // a scratch slot per part does not fit: whole ligands, a slot per workgroup
+    a.lds = sh.lds;
+    a.parts = sh.parts;
+    a.n_max = n_max;
+    a.slot_floats = sh.slot_floats(lpw_, n_max);
+    a.n_tiles = (a.n_order + lpw_ - 1) / lpw_ * sh.parts;
+    int blocks = a.n_tiles;   // parts > 1: a scratch slot per tile
+    int resident = 1;
+    if (rt::resident_workgroups(dev_, storage_, prm_.torsion_steps, sh, &resident) != EXS_OK) resident = 1;
+    if (sh.parts == 1) {
+        blocks = (int)std::max<int64_t>(1, std::min<int64_t>({(int64_t)blocks, (int64_t)resident,
+                                                              scratch_floats_ / a.slot_floats}));
+    }
     a.tile_counter = it.d_counter;
+    a.done = it.d_counter + kMaxWorkQueues;
     a.queue_bounds = d_bounds;
     a.n_queues = plan.n_queues;
     a.scratch = it.scratch;
@@ -582,9 +602,10 @@ bool Server::launch(Iteration& it) {
     a.res_coords = reinterpret_cast<float*>(it.hd_res + res_rec_bytes_);
     a.res_theta = it.hd_res + res_rec_bytes_ + res_coord_bytes_;
     hipError_t e = launch_stage_ints(it.hd_order, it.d_order, 4 * n + kMaxWorkQueues + 1, it.d_counter,
-                                     plan.n_queues, n + kMaxWorkQueues + 1, n, res_slot_, it.stream);
+                                     kMaxWorkQueues + (sh.parts > 1 ? n : 0), n + kMaxWorkQueues + 1, n,
+                                     res_slot_, it.stream);
     if (e == hipSuccess)
-        e = launch_dock(a, storage_, ppl_, std::min(resident_, a.n_tiles), threads_, lds_, it.stream);
+        e = launch_dock(a, storage_, sh, blocks, it.stream);
     if (e == hipSuccess) e = hipEventRecord(it.done, it.stream);
     if (e != hipSuccess) {
         thread_error_ = hipGetErrorString(e);
