@@ -271,45 +271,58 @@ static int dock_waves_per_cu(int lds, int waves) {
     return std::min(by_lds, kRegisterWaves / waves) * waves;
 }
 
-// Lanes per orientation, waves per workgroup and workgroups per ligand of a launch of n_lig
-// ligands.  Four lanes per orientation do the least work; where the launch then leaves SIMDs
-// without a wave, more lanes (and a wave per chunk) shorten the chain of a chunk.
+// Lanes per orientation, waves per workgroup and workgroups per ligand of a launch of n_lig ligands.
+// A launch takes about rounds + 1.2 times as long as a chunk, rounds the chunks per wave slot (1.2:
+// the largest ligands' chunks at the end).  A chunk's work is an orientation's, times the 64 / lanes
+// orientations, times kLaneCost (the work of an atom or a bond that more lanes repeat; by the turns
+// per lane), and fewer than ten waves on a CU do not use all of it.  Few lanes do the least work,
+// more lanes have shorter chunks and, with fewer poses per wave, more waves in LDS.  Measured, 4 / 8 /
+// 16 lanes (ms): 10,000 ligands of up to 60 atoms 27.2 / 27.0 / 34.3; 4,000 of up to 90 atoms, 16-bit
+// with top 8, 16.3 / 14.7 / 17.9; 1,000 ranked 4.5 / 4.6 / -; 150 of up to 128 atoms at 512
+// orientations 14.3 / 7.2 / 6.3; 13 from host memory 0.95 / 0.78 / 0.67; one 0.23 / 0.16 / 0.12.
 DockShape dock_shape(int n_lig, int n_max, int rot_max, int K, int S, int top_k, int lpw, int ppl, int cus) {
-    DockShape sh;
-    const int64_t room = (int64_t)8 * std::max(1, cus);   // waves: two per SIMD
+    const int64_t n_cu = std::max(1, cus);
     auto chunks_of = [&](int lanes) { return (K * lanes + kWave - 1) / kWave; };
-    sh.lanes = 4;
-    for (int lanes : {16, 8})
-        if (lanes <= S && (int64_t)n_lig * chunks_of(lanes) <= room) { sh.lanes = lanes; break; }
-    const int chunks = chunks_of(sh.lanes), items = lpw * chunks;
-    const int64_t total = (int64_t)n_lig * chunks;
-    auto lds_of = [&](int w) { return dock_lds(lpw, n_max, rot_max, top_k, w, sh.lanes, S); };
-    if (lpw == 1 && total <= room) {   // every chunk runs at once: spread over the CUs
-        sh.waves = total <= 2 * std::max(1, cus) ? 1 : (total <= 4 * std::max(1, cus) ? 2 : 4);
-        sh.waves = std::min(sh.waves, chunks);
-        while (sh.waves > 1 && lds_of(sh.waves).total > kDockLdsBytes) --sh.waves;
-        sh.parts = (chunks + sh.waves - 1) / sh.waves;
-    } else {
-        // the workgroup size with the most waves on a CU, less the rounds its waves do not fill
-        double best = -1.0;
-        for (int w = 1; w <= std::min(kMaxWavesPerWg, items); ++w) {
-            const int lds = lds_of(w).total;
-            if (lds > kDockLdsBytes) break;
-            const double eff = (double)items / (double)((items + w - 1) / w * w);
-            const double score = eff * dock_waves_per_cu(lds, w);
-            if (score >= best) { best = score; sh.waves = w; }
+    auto lds_of = [&](int w, int lanes) { return dock_lds(lpw, n_max, rot_max, top_k, w, lanes, S); };
+    DockShape best;
+    double best_time = -1.0;
+    for (int lanes : {4, 8, 16}) {
+        if (lanes > S) continue;
+        DockShape sh;
+        sh.lanes = lanes;
+        const int chunks = chunks_of(lanes), items = lpw * chunks;
+        const int64_t total = (int64_t)n_lig * chunks;
+        // the workgroup size with the most waves on a CU; one workgroup alone on a CU leaves it idle
+        // while it stages and finishes; 5 to 7 waves spread unevenly over the four SIMDs, and a second
+        // such workgroup does not fit beside them (150 ligands of up to 128 atoms: 14.2 ms in
+        // workgroups of 5, 7.6 in workgroups of 4)
+        double most = -1.0;
+        int on_cu = 1;
+        for (int w : {1, 2, 3, 4, 8}) {
+            const int lds = lds_of(w, lanes).total;
+            if (w > items || lds > kDockLdsBytes) break;
+            const int fit = dock_waves_per_cu(lds, w);
+            const double score = (double)items / (double)((items + w - 1) / w * w) * fit * (fit == w ? 0.8 : 1.0);
+            if (score >= most) { most = score; sh.waves = w; on_cu = fit; }
         }
+        // few chunks: spread over the CUs first
+        if (lpw == 1 && total <= 4 * n_cu) sh.waves = std::min(sh.waves, total <= 2 * n_cu ? 1 : 2);
         sh.waves = std::max(1, sh.waves / ppl);
-        if (lpw == 1) {
-            // a wave takes `each` chunks one after another; the launch is as long as its largest
-            // ligand's when that is more than about a quarter of the chunks per wave slot
-            const int64_t slots = (int64_t)std::max(1, cus) * std::max(1, dock_waves_per_cu(lds_of(sh.waves).total, sh.waves));
-            const int64_t each = std::max<int64_t>(1, total / (4 * slots));
-            sh.parts = (int)std::max<int64_t>(1, chunks / (sh.waves * each));
+        static const double kLaneCost[] = {1.8, 1.25, 1.05, 1.0};   // 1, 2, 4, 8 turns per lane
+        const int turns = S / lanes;
+        const double cost = kLaneCost[turns >= 8 ? 3 : (turns >= 4 ? 2 : (turns >= 2 ? 1 : 0))] / lanes;
+        const double rounds = (double)total / (double)(n_cu * std::max(1, on_cu));
+        const double time = cost * std::max(on_cu, 10) * (rounds + 1.2);
+        if (best_time >= 0.0 && time >= best_time) continue;
+        best_time = time;
+        if (lpw == 1) {   // a wave takes a few chunks one after another, fewer than an eighth of the rounds
+            const int each = std::max(1, (int)std::min<double>(rounds / 8.0, chunks));
+            sh.parts = (chunks + sh.waves * each - 1) / (sh.waves * each);
         }
+        best = sh;
     }
-    sh.lds = lds_of(sh.waves);
-    return sh;
+    best.lds = lds_of(best.waves, best.lanes);
+    return best;
 }
 
 }  // namespace exs

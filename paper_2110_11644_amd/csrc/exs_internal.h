@@ -154,14 +154,15 @@ inline DockLds dock_lds(int lpw, int n_max, int rot_max, int top_k, int waves, i
 }
 constexpr size_t kMaxLdsBytes = 160 * 1024;   // gfx950 LDS per workgroup
 constexpr int kDockLdsBytes = (int)kMaxLdsBytes - 256;   // dynamic LDS beside the dock kernel's static words
-// Floats in front of a scratch slot's poses: the part's best score, orientation and wave.
-constexpr int kSlotHead = 4;
+// Words in front of a scratch slot's poses: a part's best score, orientation and tau, then its
+// torsions from word 4.
+constexpr int kSlotHead = 4 + kMaxRot;
 
 // Shape of a dock launch: lanes per orientation, waves of a workgroup, workgroups per ligand.
 struct DockShape {
     int lanes = 4, waves = 1, parts = 1;
     DockLds lds{};
-    int64_t slot_floats(int lpw, int n_max) const { return kSlotHead + (int64_t)lpw * waves * 3 * n_max; }
+    int64_t slot_floats(int lpw, int n_max) const { return kSlotHead + ((int64_t)lpw * waves + (parts > 1 ? 1 : 0)) * 3 * n_max; }
 };
 DockShape dock_shape(int n_lig, int n_max, int rot_max, int K, int S, int top_k, int lpw, int ppl, int cus);
 
@@ -192,8 +193,8 @@ struct DockArgs {
     int32_t n_max;            // atoms of the largest ligand in the launch
     int32_t persistent;
     DockLds lds;
-    // scratch slots, one per workgroup (parts > 1: one per tile): a record of kSlotHead floats,
-    // then [lpw][waves][n_max][3]
+    // scratch slots, one per workgroup (parts > 1: one per tile): kSlotHead words, with parts > 1
+    // the part's pose [n_max][3], then [lpw][waves][n_max][3]
     float* scratch;
     int64_t slot_floats;
     int32_t* tile_counter;    // persistent launches: next tile of each queue [n_queues]
