@@ -40,23 +40,28 @@ __device__ __forceinline__ uint32_t to16(float v, int storage) {
 }
 
 // Expand the FP32 master [C][nz][ny][nx] (x fastest) into the gather layout, one entry per thread:
-// entry (x, y, z), index (z * (ny-1) + y) * nx + x, holds the texels of the y-z square of the node,
-// V(y, z), V(y+1, z), V(y, z+1), V(y+1, z+1) at x, as four floats (storage 0) or as four 16-bit
-// values (1 BF16, 2 FP16, rounded to nearest even).
+// entry (x, y, z) holds the texels of the y-z square of the node, V(y, z), V(y+1, z), V(y, z+1),
+// V(y+1, z+1) at x, as four floats (storage 0) or as four 16-bit values (1 BF16, 2 FP16, rounded to
+// nearest even).  The padding is neither written nor read.
 __global__ void expand_grid_kernel(const float* __restrict__ src, void* __restrict__ dst, int nx, int ny,
-                                   int64_t nxyz, int64_t per_chan, int64_t count, int storage) {
-    const int64_t nxy = (int64_t)nx * ny;
+                                   int nz, int64_t count, int storage, GatherLayout g) {
+    const int64_t nxy = (int64_t)nx * ny, chan = g.bytes / (storage == 0 ? 16 : 8);
     for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < count;
          i += (int64_t)gridDim.x * blockDim.x) {
-        const int64_t c = i / per_chan, e = i - c * per_chan;
-        const int64_t row = e / nx, z = row / (ny - 1);
-        const float* q = src + c * nxyz + z * nxy + (row - z * (ny - 1)) * nx + (e - row * nx);
+        int64_t e = i;
+        const int64_t x = e % nx;
+        e /= nx;
+        const int64_t y = e % (ny - 1);
+        e /= ny - 1;
+        const int64_t z = e % (nz - 1), c = e / (nz - 1);
+        const float* q = src + (c * nz + z) * nxy + y * nx + x;
         const float v0 = q[0], v1 = q[nx], v2 = q[nxy], v3 = q[nxy + nx];
+        const int64_t at = c * chan + z * g.slice + y * g.row + x;
         if (storage == 0)
-            static_cast<float4*>(dst)[i] = make_float4(v0, v1, v2, v3);
+            static_cast<float4*>(dst)[at] = make_float4(v0, v1, v2, v3);
         else
-            static_cast<uint2*>(dst)[i] = make_uint2(to16(v0, storage) | (to16(v1, storage) << 16),
-                                                     to16(v2, storage) | (to16(v3, storage) << 16));
+            static_cast<uint2*>(dst)[at] = make_uint2(to16(v0, storage) | (to16(v1, storage) << 16),
+                                                      to16(v2, storage) | (to16(v3, storage) << 16));
     }
 }
 
@@ -96,19 +101,14 @@ const void* dock_kernel_fn(int storage, int S, int lanes) {
     }
 }
 
-int64_t expanded_bytes(int nx, int ny, int nz, int storage) {
-    return (int64_t)nx * (ny - 1) * (nz - 1) * (storage == 0 ? 16 : 8);
-}
-
 hipError_t launch_expand_grid(const float* src, void* dst, int nx, int ny, int nz, int channels,
-                              int storage, hipStream_t st) {
-    const int64_t per_chan = (int64_t)nx * (ny - 1) * (nz - 1);
-    const int64_t count = per_chan * channels;
+                              int storage, const GatherLayout& g, hipStream_t st) {
+    const int64_t count = (int64_t)nx * (ny - 1) * (nz - 1) * channels;
     int64_t blocks = (count + 255) / 256;
     if (blocks > 65536) blocks = 65536;
     if (blocks < 1) blocks = 1;
     hipLaunchKernelGGL(expand_grid_kernel, dim3((unsigned)blocks), dim3(256), 0, st, src,
-                       dst, nx, ny, (int64_t)nx * ny * nz, per_chan, count, storage);
+                       dst, nx, ny, nz, count, storage, g);
     return hipGetLastError();
 }
 

@@ -356,7 +356,7 @@ int exs_load_pocket_grid(const float* values, int nx, int ny, int nz, int channe
                                                        : (int64_t)(nx / 2) * (ny / 2) * (nz / 2) * 128;
         if (limit_bytes > INT32_MAX)
             return fail(EXS_EINVAL, "a grid channel must expand to < 2 GiB (32 B per FP32 cell, 16 B per 16-bit cell)");
-        const int64_t tex_chan_bytes = expanded_bytes(nx, ny, nz, storage);
+        const GatherLayout layout = gather_layout(nx, ny, nz, storage);
         const int64_t count = chan * channels;
         if (!values_on_device) {
             for (int64_t i = 0; i < count; ++i) {
@@ -386,7 +386,7 @@ int exs_load_pocket_grid(const float* values, int nx, int ny, int nz, int channe
         HIP_TRY(hipMalloc(&p->master, (size_t)count * sizeof(float)));
         HIP_TRY(hipMemcpyAsync(p->master, values, (size_t)count * sizeof(float),
                                values_on_device ? hipMemcpyDeviceToDevice : hipMemcpyHostToDevice, st));
-        HIP_TRY(hipMalloc(&p->tex, (size_t)tex_chan_bytes * channels));
+        HIP_TRY(hipMalloc(&p->tex, (size_t)layout.bytes * channels));
         if (values_on_device) {   // the same checks on the device copy
             int* flag = nullptr;
             HIP_TRY(hipMallocAsync(&flag, sizeof(int), st));
@@ -401,7 +401,7 @@ int exs_load_pocket_grid(const float* values, int nx, int ny, int nz, int channe
             if (bad & 2)
                 return fail(EXS_EINVAL, "a texel overflows %s storage", storage == EXS_F16 ? "FP16" : "BF16");
         }
-        HIP_TRY(launch_expand_grid(p->master, p->tex, nx, ny, nz, channels, storage, st));
+        HIP_TRY(launch_expand_grid(p->master, p->tex, nx, ny, nz, channels, storage, layout, st));
         HIP_TRY(hipStreamSynchronize(st));
         GridDesc& g = p->desc;
         memset(&g, 0, sizeof g);
@@ -418,7 +418,9 @@ int exs_load_pocket_grid(const float* values, int nx, int ny, int nz, int channe
         g.ux_hi = nextafterf((float)(nx - 1), 0.0f);
         g.uy_hi = nextafterf((float)(ny - 1), 0.0f);
         g.uz_hi = nextafterf((float)(nz - 1), 0.0f);
-        g.chan_bytes = (int32_t)tex_chan_bytes;
+        g.chan_bytes = (int32_t)layout.bytes;
+        g.tex_row = layout.row;
+        g.tex_slice = layout.slice;
         g.master_chan_bytes = (int32_t)(chan * 4);
         g.storage = storage;
         std::lock_guard<std::mutex> lk(g_reg_mu);

@@ -99,6 +99,7 @@ struct GridDesc {
     int32_t chan_bytes;        // bytes of one channel of the gather layout
     int32_t master_chan_bytes; // bytes of one FP32 channel
     int32_t storage;           // EXS_F32 / EXS_BF16 / EXS_F16
+    int32_t tex_row, tex_slice;   // entries of a row and of a slice of the gather layout
     int32_t pad3;
 };
 
@@ -265,10 +266,30 @@ struct LigLds {
 
 // Launchers (dock_misc.hip).
 hipError_t launch_dock(const DockArgs& a, int storage, const DockShape& sh, int n_blocks, hipStream_t st);
-// Bytes of a pocket channel's gather layout: nx (ny-1)(nz-1) entries of four texels.
-int64_t expanded_bytes(int nx, int ny, int nz, int storage);
+// Gather layout of a pocket channel: entries of four texels (16 B in FP32, 8 B in 16 bits), entry
+// (x, y, z) at z * slice + y * row + x, x < nx, y < ny-1, z < nz-1.
+// The L1 serves a quad of lanes in one cycle unless two of them want the same bank of different
+// lines (or more than two lines), and rows of whole lines put every y and z of one x in the same
+// banks.  So rows and slices are padded to 6 and 3 entries past whole lines in FP32, to 12 and 9 in
+// 16 bits: of all paddings these conflict least over the quads of the turns and offsets (counted on
+// the CPU, cycles per quad, before and after: offsets 2.0 / 1.5 FP32, 2.0 / 1.4 16-bit; turns 2.3 /
+// 1.9 and 2.9 / 2.0).  A grid that the padding would take past the limits of a channel's offsets
+// goes without.
+struct GatherLayout {
+    int32_t row, slice;     // entries
+    int64_t bytes;          // of a channel
+};
+inline GatherLayout gather_layout(int nx, int ny, int nz, int storage) {
+    const int64_t eb = storage == 0 ? 16 : 8, line = 128 / eb;
+    auto pad = [line](int64_t v, int64_t rest) { return v + (rest + line - v % line) % line; };
+    const int64_t row = pad(nx, storage == 0 ? 6 : 12), slice = pad(row * (ny - 1), storage == 0 ? 3 : 9);
+    const int64_t bytes = slice * (nz - 1) * eb;
+    if (slice < (int64_t)1 << 24 && bytes <= INT32_MAX) return {(int32_t)row, (int32_t)slice, bytes};
+    const int64_t plain = (int64_t)nx * (ny - 1);
+    return {nx, (int32_t)plain, plain * (nz - 1) * eb};
+}
 hipError_t launch_expand_grid(const float* src, void* dst, int nx, int ny, int nz, int channels,
-                              int storage, hipStream_t st);
+                              int storage, const GatherLayout& g, hipStream_t st);
 // Gather probe over the pocket `gd` (device pointer) in `storage`: blocks x 256 lanes, nb
 // (8, 16 or 32) independent lookups per round.
 hipError_t launch_gather_probe(const GridDesc* gd, int storage, int nb, int64_t blocks, int per_lane,
