@@ -289,8 +289,9 @@ typedef struct {
  * on `stream` (Sec. 3.1: per ligand, restarts from the initial orientations,
  * each a greedy optimisation of the torsions and the rigid roto-translation
  * driven by the pocket score; the ligand's score is its best pose's; Sec. 3.2:
- * every ligand x pocket pair is independent).  One launch per pocket (default),
- * or one persistent launch over all pockets (EXS_FLAG_PERSISTENT).  job_out
+ * every ligand x pocket pair is independent).  One launch over all pockets of a texel
+ * storage (default), pocket by pocket, or one persistent launch over all pockets
+ * (EXS_FLAG_PERSISTENT).  job_out
  * receives the handle.  The batch and its pockets must stay loaded until the job
  * is released.
  * Errors: EXS_EINVAL (settings), EXS_ENOENT (unknown batch or a pocket
