@@ -17,6 +17,7 @@
 #include <numeric>
 #include <string>
 #include <thread>
+#include <type_traits>
 #include <unordered_map>
 #include <vector>
 
@@ -127,11 +128,19 @@ struct Pocket {
     std::atomic<int> users{0};
 };
 
+// A job's device arrays, carved from one allocation (a call each was most of a small job's time).
+// What exs_get_best_poses reads lies together: [head, coords) the scores, orientations, taus and
+// torsions, then the coordinates, then [topk, topk_end) the top_k arrays.
+struct JobLayout {
+    size_t head = 0, coords = 0, coords_end = 0, topk = 0, topk_end = 0, total = 0;
+};
+
 // A reusable execution plan of one (batch, settings) pair: device buffers that
 // outlive jobs and the launch sequence captured once in a hipGraph.
 struct Plan {
-    std::vector<void*> bufs;
+    unsigned char* block = nullptr;
     DockArgs args{};
+    JobLayout layout;
     hipGraph_t graph = nullptr;
     hipGraphExec_t exec = nullptr;
     std::atomic<bool> busy{false};
@@ -142,6 +151,7 @@ struct Batch {
     int L = 0, A = 0, R = 0, n_max = 1, rot_max = 0;
     std::vector<int32_t> pockets;          // pocket handle per table slot
     std::vector<int> storage_of_slot;
+    std::vector<int> count_of_slot;        // ligands per pocket
     std::vector<LigInfo> info;             // host copy
     std::vector<std::vector<int16_t>> mcount;   // moving-set sizes per ligand
     std::vector<int32_t> rot_base;
@@ -156,8 +166,7 @@ struct Batch {
     uint32_t* d_rot_ac = nullptr;        // [R] dihedral neighbours a | c << 16 of each rotatable bond
     void* d_block = nullptr;             // the one allocation the arrays above are carved from
     std::mutex order_mu;
-    std::map<std::vector<int>, int32_t*> d_orders;   // (S, P, T, persistent, K) -> order array
-    std::map<std::vector<int>, std::vector<int>> group_sizes;
+    std::map<std::vector<int>, int32_t*> d_orders;   // (K, S, P, T) -> order array of a persistent launch
     std::map<std::vector<int>, int> queue_counts;   // persistent orders: work queues
     std::map<std::vector<int64_t>, std::shared_ptr<Plan>> plans;   // graph plans by settings
 };
@@ -170,9 +179,10 @@ struct Job {
     hipEvent_t ev0 = nullptr, ev1 = nullptr;
     hipEvent_t ev_dock = nullptr, ev_rank = nullptr;   // eager ranked jobs: after the search, after the ranking
     int L = 0, A = 0, R = 0, K = 0, top_k = 0;
-    std::vector<void*> bufs;    // stream-ordered allocations (eager jobs)
-    std::shared_ptr<Plan> plan; // graph jobs: buffers belong to the plan
+    unsigned char* block = nullptr;   // stream-ordered allocation of the arrays (eager jobs)
+    std::shared_ptr<Plan> plan; // graph jobs: the arrays belong to the plan
     DockArgs args{};
+    JobLayout layout;
 };
 
 std::mutex g_reg_mu;
@@ -207,7 +217,7 @@ void free_batch(Batch* b) {
         Plan& pl = *kv.second;
         if (pl.exec) (void)hipGraphExecDestroy(pl.exec);
         if (pl.graph) (void)hipGraphDestroy(pl.graph);
-        for (void* q : pl.bufs) (void)hipFree(q);
+        if (pl.block) (void)hipFree(pl.block);
     }
     b->plans.clear();
 }
@@ -607,8 +617,10 @@ int exs_upload_ligands(const exs_ligand_batch* in, void* stream, int64_t* batch_
             h_grids[sl] = pk[sl]->desc;
             b->storage_of_slot.push_back(pk[sl]->storage);
         }
+        b->count_of_slot.assign(pk.size(), 0);
+        for (int l = 0; l < L; ++l) b->count_of_slot[b->info[l].pocket]++;
         // one work queue, pocket by pocket and longest first within a pocket, by the cost at the
-        // full search settings (the order of launches that cannot build one of their own)
+        // full search settings (the order of plain and of no-allocation launches)
         int32_t* up_order = reinterpret_cast<int32_t*>(hb + o_order);
         {
             std::vector<int> pocket(L);
@@ -720,92 +732,85 @@ int exs_release_ligands(int64_t batch) {
 
 namespace {
 
-// Processing order.  Plain launches: grouped by pocket, longest first in each group.
-// Persistent launch: work queues laid out by queue_plan (spread or pocket-major); the device
-// array holds the order followed by the queue bounds (kMaxWorkQueues + 1 entries reserved) and
-// *n_queues receives their count.
-int batch_order(Batch& b, int K, int S, int P, int T, int persistent, hipStream_t st,
-                int32_t** d_order, std::vector<int>* groups, int* n_queues) {
-    std::vector<int> key = {K, S, P, T, persistent};
+// Processing order of a persistent launch: work queues laid out by queue_plan (spread or
+// pocket-major); the device array holds the order followed by the queue bounds (kMaxWorkQueues + 1
+// entries reserved) and *n_queues receives their count.  (Plain launches take the upload's order.)
+int batch_order(Batch& b, int K, int S, int P, int T, hipStream_t st, int32_t** d_order, int* n_queues) {
+    std::vector<int> key = {K, S, P, T};
     std::lock_guard<std::mutex> lk(b.order_mu);
     auto it = b.d_orders.find(key);
     if (it != b.d_orders.end()) {
         *d_order = it->second;
-        *groups = b.group_sizes[key];
         *n_queues = b.queue_counts[key];
         return EXS_OK;
     }
     std::vector<double> cost(b.L);
+    std::vector<int> pocket(b.L), ord(b.L + kMaxWorkQueues + 1);
+    int used = 0;
     for (int l = 0; l < b.L; ++l) {
         cost[l] = ligand_cost(b.info[l].n, b.mcount[l].data(), b.info[l].nrot, K, S, P, T);
-        b.info[l].cost = (float)cost[l];
+        pocket[l] = b.info[l].pocket;
     }
-    std::vector<int> ord(b.L);
-    std::iota(ord.begin(), ord.end(), 0);
-    const int n_slots = (int)b.pockets.size();
-    if (persistent) {
-        std::vector<int> pocket(b.L);
-        for (int l = 0; l < b.L; ++l) pocket[l] = b.info[l].pocket;
-        int used = 0;
-        std::vector<int> seen(n_slots, 0);
-        for (int p : pocket) used += seen[p]++ == 0 ? 1 : 0;
-        const QueuePlan plan = queue_plan(b.L, used, (K + kWave - 1) / kWave);
-        ord.resize(b.L + kMaxWorkQueues + 1);
-        work_queues(b.L, pocket.data(), cost.data(), plan.n_queues, plan.pocket_major, ord.data(),
-                    ord.data() + b.L);
-        groups->assign(1, b.L);
-        *n_queues = plan.n_queues;
-    } else {
-        std::stable_sort(ord.begin(), ord.end(), [&](int a, int c) {
-            if (b.info[a].pocket != b.info[c].pocket) return b.info[a].pocket < b.info[c].pocket;
-            return cost[a] > cost[c];
-        });
-        groups->assign(n_slots, 0);
-        for (int l = 0; l < b.L; ++l) (*groups)[b.info[l].pocket]++;
-    }
+    for (int c : b.count_of_slot) used += c > 0 ? 1 : 0;
+    const QueuePlan plan = queue_plan(b.L, used, (K + kWave - 1) / kWave);
+    work_queues(b.L, pocket.data(), cost.data(), plan.n_queues, plan.pocket_major, ord.data(), ord.data() + b.L);
     int32_t* d = nullptr;
-    HIP_TRY(hipMalloc(&d, std::max<size_t>(1, ord.size()) * sizeof(int32_t)));
-    if (!ord.empty()) {
-        HIP_TRY(hipMemcpyAsync(d, ord.data(), ord.size() * sizeof(int32_t), hipMemcpyHostToDevice, st));
-        HIP_TRY(hipStreamSynchronize(st));
+    HIP_TRY(hipMalloc(&d, ord.size() * sizeof(int32_t)));
+    hipError_t e = hipMemcpyAsync(d, ord.data(), ord.size() * sizeof(int32_t), hipMemcpyHostToDevice, st);
+    if (e == hipSuccess) e = hipStreamSynchronize(st);
+    if (e != hipSuccess) {
+        (void)hipFree(d);
+        return fail(EXS_EDEVICE, "order: %s", hipGetErrorString(e));
     }
     b.d_orders[key] = d;
-    b.group_sizes[key] = *groups;
-    b.queue_counts[key] = *n_queues;
+    b.queue_counts[key] = plan.n_queues;
     *d_order = d;
+    *n_queues = plan.n_queues;
     return EXS_OK;
 }
 
-// Device buffers of a job: stream-ordered per job (eager), or plain and owned by
-// a graph plan (kept across jobs).
-struct Alloc {
-    std::vector<void*>* bufs;
-    hipStream_t stream;
-    bool stream_ordered;
-};
-
-template <class T>
-int job_alloc(Alloc& al, T** p, size_t count) {
-    size_t bytes = std::max<size_t>(count, 1) * sizeof(T);
-    void* q = nullptr;
-    if (al.stream_ordered) HIP_TRY(hipMallocAsync(&q, bytes, al.stream));
-    else HIP_TRY(hipMalloc(&q, bytes));
-    al.bufs->push_back(q);
-    *p = (T*)q;
-    return EXS_OK;
-}
-
-void free_allocs(Alloc& al) {
-    for (void* p : *al.bufs) {
-        if (al.stream_ordered) (void)hipFreeAsync(p, al.stream);
-        else (void)hipFree(p);
-    }
-    al.bufs->clear();
+// Sets the array pointers of `a` relative to `base` (null: only the sizes) and returns the layout.
+JobLayout job_layout(DockArgs& a, unsigned char* base, int64_t L, int64_t A, int64_t R, int64_t scratch_floats) {
+    JobLayout y;
+    size_t at = 0;
+    auto take = [&](auto*& p, int64_t count) {
+        using V = std::remove_reference_t<decltype(*p)>;
+        p = reinterpret_cast<V*>(base + at);
+        at += (std::max<size_t>((size_t)count, 1) * sizeof(V) + 15) & ~(size_t)15;
+    };
+    auto align = [&] { at = (at + 255) & ~(size_t)255; };
+    const int64_t K = a.K, tk = a.top_k, keep = a.rank_keep;
+    take(a.best_score, L); take(a.best_k, L); take(a.best_tau, L); take(a.best_theta, R);
+    take(a.best_score64, L);
+    y.coords = at;
+    take(a.best_coords, A * 3);
+    y.coords_end = at;
+    align();
+    y.topk = at;
+    take(a.topk_k, L * tk); take(a.topk_tau, L * tk); take(a.topk_score, L * tk);
+    take(a.topk_score64, L * tk); take(a.topk_theta, R * tk);
+    y.topk_end = at;
+    align();
+    take(a.n_clusters, L); take(a.ranked, L * keep);
+    take(a.score2, a.rescore2 ? L * keep : 0);
+    take(a.best2_k, a.rescore2 ? L : 0);
+    take(a.best2, a.rescore2 ? L : 0);
+    align();
+    take(a.orient_score, L * K); align();
+    take(a.orient_tau, L * K); align();
+    take(a.orient_theta, R * K); align();
+    take(a.final_xyz, keep > 0 ? A * 3 * K : 0); align();
+    take(a.tile_counter, kMaxWorkQueues + L);
+    a.done = a.tile_counter + kMaxWorkQueues;
+    align();
+    take(a.scratch, scratch_floats);
+    y.total = at;
+    return y;
 }
 
 void job_free(Job& j) {
-    for (void* p : j.bufs) (void)hipFreeAsync(p, j.stream);
-    j.bufs.clear();
+    if (j.block) (void)hipFreeAsync(j.block, j.stream);
+    j.block = nullptr;
     if (j.plan) { j.plan->busy = false; j.plan.reset(); }
     if (j.ev0) (void)hipEventDestroy(j.ev0);
     if (j.ev1) (void)hipEventDestroy(j.ev1);
@@ -1001,11 +1006,10 @@ int exs_dock_batch(int64_t batch, const exs_search_params* params, void* stream,
         const double* r64;
         const int32_t* order_k;
         if (int rc = orientation_tables(dev, K, &r32, &r64, &order_k)) return rc;
-        int32_t* d_order = nullptr;
-        std::vector<int> groups;
+        int32_t* d_order = b->d_upload_order;
         int n_queues = 1;
-        if (int rc = batch_order(*b, K, p.torsion_steps, p.passes, p.n_offsets, persistent, st,
-                                 &d_order, &groups, &n_queues)) return rc;
+        if (persistent)
+            if (int rc = batch_order(*b, K, p.torsion_steps, p.passes, p.n_offsets, st, &d_order, &n_queues)) return rc;
 
         auto j = std::make_shared<Job>();
         j->device = dev; j->batch = b; j->prm = p; j->stream = st;
@@ -1014,12 +1018,12 @@ int exs_dock_batch(int64_t batch, const exs_search_params* params, void* stream,
         // the launches, and the floats of pose scratch that the largest of them needs
         std::vector<DockLaunch> launches;
         int64_t scratch_floats = 1;
-        for (int gi = 0, start = 0; gi < (int)groups.size();) {
+        for (int gi = 0, start = 0; gi < (int)b->count_of_slot.size();) {
             // pockets of one texel storage share a launch: a launch each left the device idle at the
             // end of every one (2,003 ligands over 3 pockets: 3.8 ms a pass, 2.9 ms in one launch)
             const int st_g = persistent ? ls.storage : b->storage_of_slot[gi];
             int count = 0;
-            for (; gi < (int)groups.size() && (persistent || b->storage_of_slot[gi] == st_g); ++gi) count += groups[gi];
+            for (; gi < (int)b->count_of_slot.size() && (persistent || b->storage_of_slot[gi] == st_g); ++gi) count += b->count_of_slot[gi];
             if (count == 0) continue;
             DockLaunch d;
             if (int rc = plan_launch(*b, p, ls, dev, st_g, start, count, persistent, &d)) return rc;
@@ -1048,42 +1052,22 @@ int exs_dock_batch(int64_t batch, const exs_search_params* params, void* stream,
         if (plan && plan->exec) {
             j->plan = plan;
             j->args = plan->args;
+            j->layout = plan->layout;
         } else {
             DockArgs& a = j->args;
             base_args(a, *b, p, ls, r32, r64, order_k);
             std::shared_ptr<Plan> fresh;
             if (graph) fresh = std::make_shared<Plan>();
-            Alloc al{graph ? &fresh->bufs : &j->bufs, st, !graph};
-            const int R = b->R, A = b->A;
-            int rc;
-            if ((rc = job_alloc(al, &a.orient_score, (size_t)L * K)) ||
-                (rc = job_alloc(al, &a.orient_theta, (size_t)R * K)) ||
-                (rc = job_alloc(al, &a.orient_tau, (size_t)L * K)) ||
-                (rc = job_alloc(al, &a.best_score, (size_t)L)) ||
-                (rc = job_alloc(al, &a.best_k, (size_t)L)) ||
-                (rc = job_alloc(al, &a.best_coords, (size_t)A * 3)) ||
-                (rc = job_alloc(al, &a.best_theta, (size_t)R)) ||
-                (rc = job_alloc(al, &a.best_tau, (size_t)L)) ||
-                (rc = job_alloc(al, &a.best_score64, (size_t)L)) ||
-                (rc = job_alloc(al, &a.topk_k, (size_t)L * top_k)) ||
-                (rc = job_alloc(al, &a.topk_score, (size_t)L * top_k)) ||
-                (rc = job_alloc(al, &a.topk_score64, (size_t)L * top_k)) ||
-                (rc = job_alloc(al, &a.topk_theta, (size_t)R * top_k)) ||
-                (rc = job_alloc(al, &a.topk_tau, (size_t)L * top_k)) ||
-                (rc = job_alloc(al, &a.n_clusters, (size_t)L)) ||
-                (rc = job_alloc(al, &a.ranked, (size_t)L * p.rank_keep)) ||
-                (rc = job_alloc(al, &a.final_xyz, p.rank_keep > 0 ? (size_t)A * 3 * K : (size_t)0)) ||
-                (rc = job_alloc(al, &a.score2, a.rescore2 ? (size_t)L * p.rank_keep : (size_t)0)) ||
-                (rc = job_alloc(al, &a.best2_k, a.rescore2 ? (size_t)L : (size_t)0)) ||
-                (rc = job_alloc(al, &a.best2, a.rescore2 ? (size_t)L : (size_t)0)) ||
-                (rc = job_alloc(al, &a.tile_counter, (size_t)kMaxWorkQueues + L)) ||
-                (rc = job_alloc(al, &a.scratch, (size_t)scratch_floats))) {
-                free_allocs(al);
-                return rc;
-            }
-            a.done = a.tile_counter + kMaxWorkQueues;
+            const JobLayout y = job_layout(a, nullptr, L, b->A, b->R, scratch_floats);
+            unsigned char* block = nullptr;
+            if (graph) HIP_TRY(hipMalloc(&block, y.total));
+            else HIP_TRY(hipMallocAsync((void**)&block, y.total, st));
+            j->layout = job_layout(a, block, L, b->A, b->R, scratch_floats);
+            if (graph) fresh->block = block;
+            else j->block = block;
             if (graph) {
                 fresh->args = a;
+                fresh->layout = j->layout;
                 // capture the launch sequence once on a private stream
                 hipStream_t cs = nullptr;
                 HIP_TRY(hipStreamCreateWithFlags(&cs, hipStreamNonBlocking));
@@ -1100,7 +1084,7 @@ int exs_dock_batch(int64_t batch, const exs_search_params* params, void* stream,
                 if (e != hipSuccess) {
                     if (fresh->exec) (void)hipGraphExecDestroy(fresh->exec);
                     if (fresh->graph) (void)hipGraphDestroy(fresh->graph);
-                    free_allocs(al);
+                    (void)hipFree(fresh->block);
                     return fail(EXS_EDEVICE, "graph capture: %s", hipGetErrorString(e));
                 }
                 fresh->busy = true;
@@ -1142,47 +1126,52 @@ int exs_get_best_poses(int64_t job, int wait, float* best_score, exs_pose_desc* 
         if (!j) return fail(EXS_ENOENT, "unknown job %lld", (long long)job);
         if (int rc = job_wait(*j, wait)) return rc;
         const DockArgs& a = j->args;
-        const int L = j->L, R = j->R, tk = j->top_k;
-        if (best_score && tk > 0) {
-            std::vector<double> b64(L);
-            if (int rc = copy_out(b64.data(), a.best_score64, (size_t)L)) return rc;
-            for (int l = 0; l < L; ++l) best_score[l] = (float)b64[l];
-        } else if (int rc = copy_out(best_score, a.best_score, (size_t)L)) {
-            return rc;
+        const JobLayout& y = j->layout;
+        const int L = j->L, tk = j->top_k;
+        if (L == 0) return EXS_OK;
+        // the arrays of the best poses in one copy; their coordinates with them when they are few,
+        // else straight into the caller's array
+        const unsigned char* dev = reinterpret_cast<const unsigned char*>(a.best_score);
+        // array p in `copy`, the host's copy of the job's block from byte `first` on
+        auto on_host = [dev](const std::vector<unsigned char>& copy, size_t first, const auto* p) {
+            return reinterpret_cast<decltype(p)>(copy.data() + (reinterpret_cast<const unsigned char*>(p) - dev) - first);
+        };
+        const size_t coord_bytes = (size_t)j->A * 3 * sizeof(float);
+        const bool together = coords && coord_bytes <= (size_t)1 << 18;
+        std::vector<unsigned char> head;
+        if (best_score || desc || together) {
+            head.resize(together ? y.coords_end : y.coords);
+            if (int rc = copy_out(head.data(), dev, head.size())) return rc;
         }
-        if (int rc = copy_out(coords, a.best_coords, (size_t)j->A * 3)) return rc;
-        if (desc) {
-            std::vector<float> bs(L);
-            std::vector<int32_t> bk(L), bt(L);
-            std::vector<uint8_t> th(R);
-            std::vector<double> b64(L, NAN);
-            if (int rc = copy_out(bs.data(), a.best_score, (size_t)L)) return rc;
-            if (int rc = copy_out(bk.data(), a.best_k, (size_t)L)) return rc;
-            if (int rc = copy_out(bt.data(), a.best_tau, (size_t)L)) return rc;
-            if (int rc = copy_out(th.data(), a.best_theta, (size_t)R)) return rc;
-            if (tk > 0)
-                if (int rc = copy_out(b64.data(), a.best_score64, (size_t)L)) return rc;
+        if (together) memcpy(coords, on_host(head, y.head, a.best_coords), coord_bytes);
+        else if (int rc = copy_out(coords, a.best_coords, (size_t)j->A * 3)) return rc;
+        if (best_score || desc) {
+            const float* bs = on_host(head, y.head, a.best_score);
+            const int32_t* bk = on_host(head, y.head, a.best_k);
+            const int32_t* bt = on_host(head, y.head, a.best_tau);
+            const uint8_t* th = on_host(head, y.head, a.best_theta);
+            const double* b64 = on_host(head, y.head, a.best_score64);
             for (int l = 0; l < L; ++l) {
+                if (best_score) best_score[l] = tk > 0 ? (float)b64[l] : bs[l];
+                if (!desc) continue;
                 const LigInfo& inf = j->batch->info[l];
-                fill_desc(desc[l], bs[l], b64[l], bk[l], bt[l], inf.nrot, th.data() + inf.rot_base, 1);
+                fill_desc(desc[l], bs[l], tk > 0 ? b64[l] : NAN, bk[l], bt[l], inf.nrot, th + inf.rot_base, 1);
             }
         }
         if (topk && tk > 0) {
-            std::vector<int32_t> kk((size_t)L * tk), tt((size_t)L * tk);
-            std::vector<float> sc((size_t)L * tk);
-            std::vector<double> s64((size_t)L * tk);
-            std::vector<uint8_t> th((size_t)R * tk);
-            if (int rc = copy_out(kk.data(), a.topk_k, kk.size())) return rc;
-            if (int rc = copy_out(tt.data(), a.topk_tau, tt.size())) return rc;
-            if (int rc = copy_out(sc.data(), a.topk_score, sc.size())) return rc;
-            if (int rc = copy_out(s64.data(), a.topk_score64, s64.size())) return rc;
-            if (int rc = copy_out(th.data(), a.topk_theta, th.size())) return rc;
+            std::vector<unsigned char> top(y.topk_end - y.topk);
+            if (int rc = copy_out(top.data(), dev + y.topk, top.size())) return rc;
+            const int32_t* kk = on_host(top, y.topk, a.topk_k);
+            const int32_t* tt = on_host(top, y.topk, a.topk_tau);
+            const float* sc = on_host(top, y.topk, a.topk_score);
+            const double* s64 = on_host(top, y.topk, a.topk_score64);
+            const uint8_t* th = on_host(top, y.topk, a.topk_theta);
             for (int l = 0; l < L; ++l) {
                 const LigInfo& inf = j->batch->info[l];
                 for (int t = 0; t < tk; ++t) {
-                    size_t o = (size_t)l * tk + t;
+                    const size_t o = (size_t)l * tk + t;
                     fill_desc(topk[o], sc[o], s64[o], kk[o], tt[o], inf.nrot,
-                              th.data() + (size_t)inf.rot_base * tk + t, (size_t)tk);
+                              th + (size_t)inf.rot_base * tk + t, (size_t)tk);
                 }
             }
         }
