@@ -201,8 +201,9 @@ __host__ __device__ inline int orientation_bands(int K) {
     return b;
 }
 __global__ void orientation_table_kernel(int K, float* __restrict__ r32, double* __restrict__ r64,
-                                         int32_t* __restrict__ order_k) {
+                                         int32_t* __restrict__ order_k, int32_t* __restrict__ zero, int n_zero) {
     const int k = blockIdx.x * blockDim.x + threadIdx.x;
+    for (int t = k; t < n_zero; t += gridDim.x * blockDim.x) zero[t] = 0;
     if (k >= K) return;
     const double golden = 3.14159265358979323846 * (3.0 - sqrt(5.0));
     const double zk = 1.0 - (2.0 * k + 1.0) / (double)K;
@@ -229,8 +230,10 @@ __global__ void orientation_table_kernel(int K, float* __restrict__ r32, double*
     order_k[at] = k;
 }
 
-hipError_t launch_orientation_table(int K, float* r32, double* r64, int32_t* order_k, hipStream_t st) {
-    hipLaunchKernelGGL(orientation_table_kernel, dim3((K + 63) / 64), dim3(64), 0, st, K, r32, r64, order_k);
+hipError_t launch_orientation_table(int K, float* r32, double* r64, int32_t* order_k, int32_t* zero, int n_zero,
+                                    hipStream_t st) {
+    hipLaunchKernelGGL(orientation_table_kernel, dim3((K + 63) / 64), dim3(64), 0, st, K, r32, r64, order_k, zero,
+                       n_zero);
     return hipGetLastError();
 }
 

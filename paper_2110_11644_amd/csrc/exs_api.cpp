@@ -96,7 +96,7 @@ int orientation_tables(int dev, int K, const float** r32, const double** r64, co
         HIP_TRY(hipMalloc(&t.r32, (size_t)K * 9 * sizeof(float)));
         HIP_TRY(hipMalloc(&t.r64, (size_t)K * 9 * sizeof(double)));
         HIP_TRY(hipMalloc(&t.order, (size_t)K * sizeof(int32_t)));
-        HIP_TRY(launch_orientation_table(K, t.r32, t.r64, t.order, nullptr));
+        HIP_TRY(launch_orientation_table(K, t.r32, t.r64, t.order, nullptr, 0, nullptr));
         HIP_TRY(hipStreamSynchronize(nullptr));
         it = d.orient_tables.emplace(K, t).first;
     }

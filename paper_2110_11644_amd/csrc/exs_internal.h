@@ -314,8 +314,9 @@ hipError_t launch_stage_ints(const int32_t* src, int32_t* dst, int n, int* zero,
 // *flag |= 1 if a texel is not finite, |= 2 if one overflows the 16-bit storage (storage 1, 2).
 hipError_t launch_check_texels(const float* v, int64_t count, int storage, int* flag, hipStream_t st);
 // K orientation matrices [K][9] (row-major), FP32 and (unless r64 is null) FP64, and the order in
-// which the chunks take the orientations [K].
-hipError_t launch_orientation_table(int K, float* r32, double* r64, int32_t* order_k, hipStream_t st);
+// which the chunks take the orientations [K]; clears zero[0 .. n_zero) (launch counters) as well.
+hipError_t launch_orientation_table(int K, float* r32, double* r64, int32_t* order_k, int32_t* zero, int n_zero,
+                                    hipStream_t st);
 hipError_t upload_trig_tables();
 const void* dock_kernel_fn(int storage, int S, int lanes);
 

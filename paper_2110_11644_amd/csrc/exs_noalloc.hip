@@ -90,13 +90,17 @@ extern "C" int exs_dock_batch_noalloc(int64_t batch, const exs_search_params* pa
     int32_t* order_k = c.take<int32_t>((size_t)K);
     a.order_k = order_k;
     const size_t slot_bytes = (size_t)a.slot_floats * sizeof(float);
-    if (a.parts > 1) a.done = c.take<int32_t>((size_t)L);
+    if (a.parts > 1) {   // the counters side by side
+        a.tile_counter = c.take<int32_t>(kMaxWorkQueues + (size_t)L);
+        a.done = a.tile_counter + kMaxWorkQueues;
+    }
     const int64_t fit = std::max<int64_t>(0, (int64_t)kScratchBytes - (int64_t)c.used) / (int64_t)slot_bytes;
     if (a.parts > 1 && fit < pl.blocks) {   // a slot per tile does not fit: whole ligands, a slot per workgroup
         a.parts = 1;
         a.n_tiles = (int)((L + a.lpw - 1) / a.lpw);
     }
-    const int blocks = (int)std::max<int64_t>(1, std::min<int64_t>(pl.blocks, fit));
+    if (fit < 1) return rt::fail(EXS_EINVAL, "the no-allocation buffer does not hold a workgroup's scratch (split the batch)");
+    const int blocks = (int)std::min<int64_t>(pl.blocks, fit);
     a.scratch = c.take<float>((size_t)blocks * a.slot_floats);
     a.best_score = best_score;
     a.best_k = best_orient;
@@ -104,9 +108,10 @@ extern "C" int exs_dock_batch_noalloc(int64_t batch, const exs_search_params* pa
     a.best_theta = best_theta;
     a.best_coords = best_coords;
     hipStream_t st = static_cast<hipStream_t>(stream);
-    hipError_t e = launch_orientation_table((int)K, rot32, nullptr, order_k, st);
-    if (e == hipSuccess) e = launch_zero_ints(a.tile_counter, kMaxWorkQueues, st);
-    if (e == hipSuccess && a.parts > 1) e = launch_zero_ints(a.done, (int)L, st);
+    // one kernel builds the table and clears the counters: a launch each for them took 10 of a
+    // single ligand's 150 us
+    hipError_t e = launch_orientation_table((int)K, rot32, nullptr, order_k, a.tile_counter,
+                                            kMaxWorkQueues + (a.parts > 1 ? (int)L : 0), st);
     if (e == hipSuccess) e = launch_dock(a, pl.storage, pl.shape, blocks, st);
     if (e != hipSuccess) return rt::fail(EXS_EDEVICE, "no-allocation launch: %s", hipGetErrorString(e));
     return EXS_OK;
