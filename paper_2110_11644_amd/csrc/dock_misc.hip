@@ -114,11 +114,10 @@ hipError_t launch_expand_grid(const float* src, void* dst, int nx, int ny, int n
 
 hipError_t launch_rank(const DockArgs& a, int n_lig, const int32_t* order, hipStream_t st) {
     if (n_lig <= 0) return hipSuccess;
-    // up to 4 waves (ligands) per block, within 64 KB of LDS
-    const size_t per_wave = (size_t)rank_lds_words(a.K, a.n_max) * sizeof(int);
-    const int waves = (int)std::max<size_t>(1, std::min<size_t>(4, (64 * 1024) / per_wave));
-    hipLaunchKernelGGL(rank_kernel, dim3((n_lig + waves - 1) / waves), dim3(waves * kWave),
-                       waves * per_wave, st, a, n_lig, order);
+    // a wave for every 64 poses of a ligand, at most kRankWaves
+    const int waves = std::min(kRankWaves, (a.K + kWave - 1) / kWave);
+    hipLaunchKernelGGL(rank_kernel, dim3(n_lig), dim3(waves * kWave),
+                       (size_t)rank_lds_words(a.K, a.n_max) * sizeof(int), st, a, n_lig, order);
     return hipGetLastError();
 }
 

@@ -247,11 +247,19 @@ struct DockArgs {
     uint8_t* res_theta;
 };
 
-// LDS words per wave of the ranking kernel: rank, state and score per pose, the leader bits,
-// the coordinates of 8 candidate leaders (3 n_max rows each, n_max the launch's largest
-// ligand) and the list of uncovered poses.
+// LDS words of a ranking block: a head of rank, state and score per pose, the leader bits, the
+// list of uncovered poses and the waves' shares of it (to a multiple of 4 words), then the
+// coordinates of 8 candidate leaders (rank_row_words rows each, n_max the launch's largest ligand).
+constexpr int kRankWaves = 4;
+constexpr int kRankRowBatch = 16;   // pose rows a sweep loads at once; a candidate's rows are padded to it
+__host__ __device__ inline int rank_row_words(int n_max) {
+    return (3 * n_max + kRankRowBatch - 1) / kRankRowBatch * kRankRowBatch;
+}
+__host__ __device__ inline int rank_head_words(int K) {
+    return (4 * K + (K + 31) / 32 + kRankWaves + 2 + 3) & ~3;
+}
 __host__ __device__ inline int rank_lds_words(int K, int n_max) {
-    return 4 * K + (K + 31) / 32 + 8 * 3 * n_max;
+    return rank_head_words(K) + 8 * (rank_row_words(n_max) + 4);
 }
 
 // A ligand's topology in the LDS of the second-stage rescoring.
@@ -300,7 +308,7 @@ hipError_t launch_gather_probe(const GridDesc* gd, int storage, int nb, int64_t 
 hipError_t launch_unfold(const LigInfo* info, float4* ref, double* ref64, const uint32_t* rot_uv,
                          const uint4* rot_mask, int32_t* turns, const int32_t* order, int n_lig, int R,
                          int S, int passes, hipStream_t st);
-// Ranking of the final poses of `n_lig` ligands (rank_keep > 0), one wave per ligand, the
+// Ranking of the final poses of `n_lig` ligands (rank_keep > 0), one block per ligand, the
 // ligands taken in `order` (a permutation of 0..n_lig-1, longest first).
 hipError_t launch_rank(const DockArgs& a, int n_lig, const int32_t* order, hipStream_t st);
 // Second-stage rescoring of the ranked poses of `n_lig` ligands, one block of waves per ligand,
