@@ -133,13 +133,10 @@ hipError_t launch_unfold(const LigInfo* info, float4* ref, double* ref64, const 
                          int S, int passes, hipStream_t st) {
     if (n_lig <= 0) return hipSuccess;
     UnfoldArgs a{info, ref, ref64, rot_uv, rot_mask, turns, order, n_lig, R, passes, 0};
-    constexpr int kWavesPerBlock = 4;
-    const dim3 grid((n_lig + kWavesPerBlock - 1) / kWavesPerBlock), block(kWavesPerBlock * kWave);
-    const size_t lds = (size_t)kWavesPerBlock * kUnfoldLdsPerWave;
     switch (S) {
-        case 8: hipLaunchKernelGGL(unfold_kernel<8>, grid, block, lds, st, a); break;
-        case 16: hipLaunchKernelGGL(unfold_kernel<16>, grid, block, lds, st, a); break;
-        case 32: hipLaunchKernelGGL(unfold_kernel<32>, grid, block, lds, st, a); break;
+        case 8: hipLaunchKernelGGL(unfold_kernel<8>, dim3(n_lig), dim3(64), 0, st, a); break;
+        case 16: hipLaunchKernelGGL(unfold_kernel<16>, dim3(n_lig), dim3(128), 0, st, a); break;
+        case 32: hipLaunchKernelGGL(unfold_kernel<32>, dim3(n_lig), dim3(256), 0, st, a); break;
         default: return hipErrorInvalidValue;
     }
     return hipGetLastError();
