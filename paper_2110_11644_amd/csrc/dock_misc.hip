@@ -123,8 +123,8 @@ hipError_t launch_rank(const DockArgs& a, int n_lig, const int32_t* order, hipSt
 
 hipError_t launch_rescore2(const DockArgs& a, int n_lig, const int32_t* order, hipStream_t st) {
     if (n_lig <= 0) return hipSuccess;
-    hipLaunchKernelGGL(rescore2_kernel, dim3(n_lig), dim3(kRescoreWaves * kWave),
-                       rescore2_lds_bytes(kRescoreWaves), st, a, n_lig, order);
+    const int waves = rescore2_waves(n_lig, a.rank_keep);
+    hipLaunchKernelGGL(rescore2_kernel, dim3(n_lig), dim3(waves * kWave), rescore2_lds_bytes(waves), st, a, n_lig, order);
     return hipGetLastError();
 }
 
