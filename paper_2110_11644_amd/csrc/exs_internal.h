@@ -16,15 +16,18 @@ constexpr int kMaxThreadsPerWg = kMaxWavesPerWg * kWave;
 constexpr int kXcds = 8;   // accelerator complex dies of an MI355X, each with its own L2
 
 // Work queues of a persistent launch: the workgroups of XCD x start on queue x % n_queues and
-// move on to the others once it is drained.  Two layouts of the order:
+// move on to the others once it is drained.  Three layouts of the order:
+//  * one queue, longest first, for one pocket: what runs last is short.  (Cut into queues, the one of
+//    the longest ligands ends in long ones too: 230 ligands of up to 90 atoms 1,377 us, 903 in one
+//    queue; 1,000 of up to 60 3.13 and 2.93 ms.)
 //  * spread: kXcds queues, contiguous pocket-major runs of equal cost, each longest first.  For
-//    launches whose pockets hold fewer ligands each than the device has in flight: all of the
-//    launch runs at once and its tail decides (serving iterations of <= 4,096 ligands over 15
-//    pockets: capacity 152k docks/s, against 127k pocket by pocket).
+//    launches whose pockets hold fewer ligands each than the device has in flight: an XCD's
+//    workgroups keep to one or two pockets (6,000 ligands over 5 pockets of 96^3 x 8, FP32: 15.3 ms,
+//    15.8 pocket by pocket, 26.5 in one queue longest first).
 //  * pocket-major: kPocketMajorQueues queues, each pocket by pocket, longest first within a
 //    pocket, so that few pockets are in use at a time and their texel blocks stay in the L2s and
-//    the shared last-level cache (100,000 ligands over 15 pockets, FP32: 634 ms spread; 567,
-//    543, 548 ms with 1, 2, 4 pocket-major queues).
+//    the shared last-level cache (4,000 ligands over 4 pockets of 128^3 x 8, BF16: 12.2 ms, 13.0 in
+//    one such queue, 13.2 spread).
 constexpr int kMaxWorkQueues = kXcds;
 constexpr int kPocketMajorQueues = 2;
 constexpr int kInflightWaves = 256 * 4 * 3;   // CUs x SIMDs x dock-kernel waves per SIMD
@@ -34,6 +37,7 @@ struct QueuePlan {
 };
 // Layout for n_ligands ligands over n_pockets distinct pockets, waves_per_ligand waves each.
 inline QueuePlan queue_plan(int64_t n_ligands, int n_pockets, int waves_per_ligand) {
+    if (n_pockets <= 1) return {1, false};
     const int64_t inflight = kInflightWaves / (waves_per_ligand > 0 ? waves_per_ligand : 1);
     if (n_pockets >= 2 && n_ligands >= inflight * n_pockets) return {kPocketMajorQueues, true};
     return {kXcds, false};

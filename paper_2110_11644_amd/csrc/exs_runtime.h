@@ -30,6 +30,7 @@ void pocket_use(int32_t id, int delta);                   // pin / unpin against
 struct NoAllocPlan {
     DockArgs args{};
     int device = 0, storage = 0, blocks = 1;
+    int64_t slots = 1;         // scratch slots
     DockShape shape;
     int64_t limit_bytes = 0;   // what the buffer's limit counts for one workgroup
     int64_t L = 0, A = 0, R = 0;

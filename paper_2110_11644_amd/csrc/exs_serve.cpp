@@ -580,13 +580,11 @@ bool Server::launch(Iteration& it) {
     a.n_max = n_max;
     a.slot_floats = sh.slot_floats(lpw_, n_max);
     a.n_tiles = (a.n_order + lpw_ - 1) / lpw_ * sh.parts;
-    int blocks = a.n_tiles;   // parts > 1: a scratch slot per tile
     int resident = 1;
     if (rt::resident_workgroups(dev_, storage_, prm_.torsion_steps, sh, &resident) != EXS_OK) resident = 1;
-    if (sh.parts == 1) {
-        blocks = (int)std::max<int64_t>(1, std::min<int64_t>({(int64_t)blocks, (int64_t)resident,
-                                                              scratch_floats_ / a.slot_floats}));
-    }
+    int64_t blocks = std::min(a.n_tiles, resident);
+    if (sh.parts == 1) blocks = std::min(blocks, scratch_floats_ / a.slot_floats);   // parts > 1: a slot per tile
+    blocks = std::max<int64_t>(1, blocks);
     a.tile_counter = it.d_counter;
     a.done = it.d_counter + kMaxWorkQueues;
     a.queue_bounds = d_bounds;
@@ -605,7 +603,7 @@ bool Server::launch(Iteration& it) {
                                      kMaxWorkQueues + (sh.parts > 1 ? n : 0), n + kMaxWorkQueues + 1, n,
                                      res_slot_, it.stream);
     if (e == hipSuccess)
-        e = launch_dock(a, storage_, sh, blocks, it.stream);
+        e = launch_dock(a, storage_, sh, (int)blocks, it.stream);
     if (e == hipSuccess) e = hipEventRecord(it.done, it.stream);
     if (e != hipSuccess) {
         thread_error_ = hipGetErrorString(e);
