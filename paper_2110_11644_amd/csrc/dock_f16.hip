@@ -12,7 +12,7 @@ hipError_t launch_dock_f16(const DockArgs& a, int lanes, dim3 grid, dim3 block, 
         return hipGetLastError(); \
     }
     EXS_LAUNCH(8, 4) EXS_LAUNCH(8, 8) EXS_LAUNCH(16, 4) EXS_LAUNCH(16, 8) EXS_LAUNCH(16, 16)
-    EXS_LAUNCH(32, 4) EXS_LAUNCH(32, 8) EXS_LAUNCH(32, 16)
+    EXS_LAUNCH(32, 4) EXS_LAUNCH(32, 8) EXS_LAUNCH(32, 16) EXS_LAUNCH(32, 32)
 #undef EXS_LAUNCH
     return hipErrorInvalidValue;
 }
@@ -21,7 +21,7 @@ const void* dock_kernel_fn_f16(int S, int lanes) {
 #define EXS_FN(SS, GG) \
     if (S == SS && lanes == GG) return reinterpret_cast<const void*>(&dock_kernel<SS, GG, TexF16>);
     EXS_FN(8, 4) EXS_FN(8, 8) EXS_FN(16, 4) EXS_FN(16, 8) EXS_FN(16, 16)
-    EXS_FN(32, 4) EXS_FN(32, 8) EXS_FN(32, 16)
+    EXS_FN(32, 4) EXS_FN(32, 8) EXS_FN(32, 16) EXS_FN(32, 32)
 #undef EXS_FN
     return nullptr;
 }

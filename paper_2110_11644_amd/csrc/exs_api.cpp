@@ -11,6 +11,7 @@
 
 #include <algorithm>
 #include <atomic>
+#include <cmath>
 #include <map>
 #include <memory>
 #include <mutex>
@@ -281,22 +282,39 @@ static int dock_waves_per_cu(int lds, int waves) {
     return std::min(by_lds, kRegisterWaves / waves) * waves;
 }
 
+// Work of an orientation by its lanes, over that with four: more lanes repeat an atom's or a bond's
+// share in more places, which counts the more the fewer turns each has.  From the times of full
+// launches.
+static double lane_cost(int lanes, int S) {
+    switch (lanes) {
+        case 8: return S == 32 ? 1.0 : (S == 16 ? 1.16 : 1.1);
+        case 16: return S == 32 ? 1.24 : 1.48;
+        case 32: return 1.7;
+        default: return 1.0;
+    }
+}
+
 // Lanes per orientation, waves per workgroup and workgroups per ligand of a launch of n_lig ligands.
-// A launch takes about rounds + 1.2 times as long as a chunk, rounds the chunks per wave slot (1.2:
-// the largest ligands' chunks at the end).  A chunk's work is an orientation's, times the 64 / lanes
-// orientations, times kLaneCost (the work of an atom or a bond that more lanes repeat; by the turns
-// per lane), and fewer than ten waves on a CU do not use all of it.  Few lanes do the least work,
-// more lanes have shorter chunks and, with fewer poses per wave, more waves in LDS.  Measured, 4 / 8 /
-// 16 lanes (ms): 10,000 ligands of up to 60 atoms 27.2 / 27.0 / 34.3; 4,000 of up to 90 atoms, 16-bit
-// with top 8, 16.3 / 14.7 / 17.9; 1,000 ranked 4.5 / 4.6 / -; 150 of up to 128 atoms at 512
-// orientations 14.3 / 7.2 / 6.3; 13 from host memory 0.95 / 0.78 / 0.67; one 0.23 / 0.16 / 0.12.
-DockShape dock_shape(int n_lig, int n_max, int rot_max, int K, int S, int top_k, int lpw, int ppl, int cus) {
+// A launch takes as long as its rounds, the chunks per wave slot, but no less than kAloneRounds of
+// them: the longest ligand's chunk, alone on the chip.  (Both count about equally where they are equal;
+// the fourth power fits the times between.)  A chunk's work is an orientation's, times the
+// 64 / lanes orientations, times lane_cost, and fewer than eleven waves on a CU do not use all of it.
+// Few lanes do the least work, more lanes have shorter chunks and, with fewer poses per wave, more
+// waves in LDS.  Measured with 4 / 8 / 16 / 32 lanes (us), 256 orientations of 32 turns, up to 60 atoms:
+// 20 ligands 659 / 440 / 309 / 250, 60: 691 / 446 / 318 / 324, 90: 750 / 498 / 383 / 515, 256: 938 /
+// 720 / 923 / 1,228, 1,000: 2,780 / 2,760 / 3,430 / 4,820, 10,000: 25,310 / 24,980 / - / -; 16-bit, up
+// to 90 atoms, 90: 1,220 / 740 / 518 / 611, 1,000: 4,540 / 3,290 / 4,140 / 6,100; 16 turns, 1,000:
+// 1,872 / 2,024 / 2,789; 8 turns of 100 orientations, 512: 700 / 490.  `beside`: ligands of another
+// launch that shares the chip, which count in the rounds (a served burst in shapes for each iteration
+// alone: 5.8 ms, 4.2 with the other's).
+constexpr double kAloneRounds = 2.2;
+DockShape dock_shape(int n_lig, int beside, int n_max, int rot_max, int K, int S, int top_k, int lpw, int ppl, int cus) {
     const int64_t n_cu = std::max(1, cus);
     auto chunks_of = [&](int lanes) { return (K * lanes + kWave - 1) / kWave; };
     auto lds_of = [&](int w, int lanes) { return dock_lds(lpw, n_max, rot_max, top_k, w, lanes, S); };
     DockShape best;
     double best_time = -1.0;
-    for (int lanes : {4, 8, 16}) {
+    for (int lanes : {4, 8, 16, 32}) {
         if (lanes > S) continue;
         DockShape sh;
         sh.lanes = lanes;
@@ -305,28 +323,30 @@ DockShape dock_shape(int n_lig, int n_max, int rot_max, int K, int S, int top_k,
         // the workgroup size with the most waves on a CU; one workgroup alone on a CU leaves it idle
         // while it stages and finishes; 5 to 7 waves spread unevenly over the four SIMDs, and a second
         // such workgroup does not fit beside them (150 ligands of up to 128 atoms: 14.2 ms in
-        // workgroups of 5, 7.6 in workgroups of 4)
+        // workgroups of 5, 7.6 in workgroups of 4).  Where as many fit, fewer waves wait less for each
+        // other (256 ligands of up to 60 atoms in workgroups of 1, 2 and 4: 718, 750 and 782 us); but
+        // with top_k every workgroup takes part in the selection (4,000 ligands, top 8, in 4 and in 2:
+        // 12.6 and 13.0 ms)
         double most = -1.0;
         int on_cu = 1;
         for (int w : {1, 2, 3, 4, 8}) {
             const int lds = lds_of(w, lanes).total;
             if (w > items || lds > kDockLdsBytes) break;
             const int fit = dock_waves_per_cu(lds, w);
-            const double score = (double)items / (double)((items + w - 1) / w * w) * fit * (fit == w ? 0.8 : 1.0);
+            const double wait = top_k > 0 || lpw > 1 ? 1.0 : 1.0 - 0.012 * (w - 1);
+            const double score = (double)items / (double)((items + w - 1) / w * w) * fit * (fit == w ? 0.8 : 1.0) * wait;
             if (score >= most) { most = score; sh.waves = w; on_cu = fit; }
         }
         // few chunks: spread over the CUs first
         if (lpw == 1 && total <= 4 * n_cu) sh.waves = std::min(sh.waves, total <= 2 * n_cu ? 1 : 2);
         sh.waves = std::max(1, sh.waves / ppl);
-        static const double kLaneCost[] = {1.8, 1.25, 1.05, 1.0};   // 1, 2, 4, 8 turns per lane
-        const int turns = S / lanes;
-        const double cost = kLaneCost[turns >= 8 ? 3 : (turns >= 4 ? 2 : (turns >= 2 ? 1 : 0))] / lanes;
-        const double rounds = (double)total / (double)(n_cu * std::max(1, on_cu));
-        const double time = cost * std::max(on_cu, 10) * (rounds + 1.2);
+        const double rounds = (double)(n_lig + beside) * chunks / (double)(n_cu * std::max(1, on_cu));
+        const double time = lane_cost(lanes, S) / lanes * std::max(on_cu, 11) *
+                            std::pow(std::pow(rounds, 4.0) + std::pow(kAloneRounds, 4.0), 0.25);
         if (best_time >= 0.0 && time >= best_time) continue;
         best_time = time;
-        if (lpw == 1) {   // a wave takes a few chunks one after another, fewer than an eighth of the rounds
-            const int each = std::max(1, (int)std::min<double>(rounds / 8.0, chunks));
+        if (lpw == 1) {   // a wave takes a few chunks one after another, fewer than a tenth of the rounds
+            const int each = std::max(1, (int)std::min<double>(rounds / 10.0, chunks));
             sh.parts = (chunks + sh.waves * each - 1) / (sh.waves * each);
         }
         best = sh;
@@ -971,7 +991,7 @@ void base_args(DockArgs& a, const Batch& b, const exs_search_params& p, const La
 // The launch of `count` ligands of batch b, from position `start` of the order.
 int plan_launch(const Batch& b, const exs_search_params& p, const LaunchSettings& ls, int dev, int storage,
                 int start, int count, bool persistent, DockLaunch* out) {
-    out->shape = dock_shape(count, b.n_max, b.rot_max, p.n_orient, p.torsion_steps, ls.top_k, ls.lpw, ls.ppl,
+    out->shape = dock_shape(count, 0, b.n_max, b.rot_max, p.n_orient, p.torsion_steps, ls.top_k, ls.lpw, ls.ppl,
                             rt::device_cus(dev));
     out->storage = storage;
     out->start = start;

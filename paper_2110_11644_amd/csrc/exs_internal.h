@@ -169,7 +169,7 @@ struct DockShape {
     DockLds lds{};
     int64_t slot_floats(int lpw, int n_max) const { return kSlotHead + ((int64_t)lpw * waves + (parts > 1 ? 1 : 0)) * 3 * n_max; }
 };
-DockShape dock_shape(int n_lig, int n_max, int rot_max, int K, int S, int top_k, int lpw, int ppl, int cus);
+DockShape dock_shape(int n_lig, int beside, int n_max, int rot_max, int K, int S, int top_k, int lpw, int ppl, int cus);
 
 // Everything one dock launch reads and writes.
 struct DockArgs {

@@ -95,13 +95,13 @@ extern "C" int exs_dock_batch_noalloc(int64_t batch, const exs_search_params* pa
         a.done = a.tile_counter + kMaxWorkQueues;
     }
     const int64_t fit = std::max<int64_t>(0, (int64_t)kScratchBytes - (int64_t)c.used) / (int64_t)slot_bytes;
-    if (a.parts > 1 && fit < pl.slots) {   // a slot per tile does not fit: whole ligands, a slot per workgroup
-        a.parts = 1;
-        a.n_tiles = (int)((L + a.lpw - 1) / a.lpw);
+    if (a.parts > 1 && fit < pl.slots) {   // a slot per part: as many parts as fit; at one, a slot per workgroup
+        a.parts = (int)std::max<int64_t>(1, fit / L);
+        a.n_tiles = (int)((L + a.lpw - 1) / a.lpw) * a.parts;
     }
     if (fit < 1) return rt::fail(EXS_EINVAL, "the no-allocation buffer does not hold a workgroup's scratch (split the batch)");
-    const int blocks = (int)std::min<int64_t>(pl.blocks, fit);
-    a.scratch = c.take<float>((size_t)(a.parts > 1 ? pl.slots : blocks) * a.slot_floats);
+    const int blocks = (int)std::min<int64_t>({(int64_t)pl.blocks, fit, (int64_t)a.n_tiles});
+    a.scratch = c.take<float>((size_t)(a.parts > 1 ? a.n_tiles : blocks) * a.slot_floats);
     a.best_score = best_score;
     a.best_k = best_orient;
     a.best_tau = best_tau;

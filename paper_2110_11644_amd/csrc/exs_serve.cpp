@@ -168,6 +168,7 @@ struct Iteration {
     unsigned char* h_res = nullptr;
     unsigned char* hd_res = nullptr;
     bool running = false;
+    int n_lig = 0;
     struct Work { Request* r; int start, count; };   // ligands start .. start+count-1 of r
     std::vector<Work> work;
     Clock::time_point t_launch;
@@ -572,9 +573,13 @@ bool Server::launch(Iteration& it) {
     // the launch's shape from its own largest ligand
     const int n_max = std::max(1, (int)*std::max_element(nat.begin(), nat.end()));
     const int rot_max = *std::max_element(nrt.begin(), nrt.end());
-    DockShape sh = dock_shape(n, n_max, rot_max, K_, prm_.torsion_steps, top_k_, lpw_, ppl_, rt::device_cus(dev_));
-    if (sh.parts > 1 && (int64_t)n * sh.parts * sh.slot_floats(lpw_, n_max) > scratch_floats_)
-        sh.parts = 1;   // a scratch slot per part does not fit: whole ligands, a slot per workgroup
+    int beside = 0;   // ligands of the iterations that share the chip with this one
+    for (int i = 0; i < n_iters_; ++i)
+        if (it_[i].running) beside += it_[i].n_lig;
+    it.n_lig = n;
+    DockShape sh = dock_shape(n, beside, n_max, rot_max, K_, prm_.torsion_steps, top_k_, lpw_, ppl_, rt::device_cus(dev_));
+    if (sh.parts > 1)   // a scratch slot per part: as many parts as fit; at one, a slot per workgroup
+        sh.parts = (int)std::max<int64_t>(1, std::min<int64_t>(sh.parts, scratch_floats_ / (n * sh.slot_floats(lpw_, n_max))));
     a.lds = sh.lds;
     a.parts = sh.parts;
     a.n_max = n_max;

@@ -1,6 +1,6 @@
 """GPU: the dock launch at the sizes where its shape changes.
 
-The launch picks lanes per orientation (4, 8 or 16) and workgroups per ligand from the number of
+The launch picks lanes per orientation (4, 8, 16 or 32) and workgroups per ligand from the number of
 ligands and orientations; the wave's loops have remainders at atom counts around the exclusion
 words, the lane groups and the limits.  Results must be the oracle's (tests/parity.py) for one
 copy of the ligands and bit for bit the same for many copies, per pocket and persistent; thin
@@ -11,7 +11,7 @@ import pytest
 
 import exs_synth as S
 from parity import check_ligand
-from test_gpu_parity import run
+from test_gpu_parity import check_topk, run
 
 pytestmark = pytest.mark.gpu
 
@@ -82,3 +82,42 @@ def test_thin_grids(B, oracle_lib, storage, edges):
     batch = S.batch_from_ligands(ligands([6, 9], 2, 3, index=1))
     out = run(B, [p], batch, s, storage=storage)
     check(O, grid, s, batch, out, 2)
+
+
+@pytest.mark.parametrize("K,copies", [(37, 1), (37, 45), (130, 1), (130, 300)])
+def test_top_poses_in_every_launch_shape(B, oracle_lib, K, copies):
+    p = S.make_pocket("small")
+    s = S.SearchSettings(K, 32, 1, 27)
+    ligs = ligands([1, 9, 40, 128], 6, p.channels)
+    print("top poses K %d copies %d" % (K, copies), flush=True)
+    out = run(B, [p], S.batch_from_ligands(ligs * copies), s, top_k=8)
+    one = {k: out[k][:len(ligs)] for k in ("score", "topk", "best", "best_score")}
+    one["coords"] = out["coords"]
+    check_topk(oracle_lib, oracle_lib.Grid.of(p), s, S.batch_from_ligands(ligs), one, 8)
+    for key in ("score", "best_score", "topk"):
+        a = out[key].reshape((copies, len(ligs)) + out[key].shape[1:])
+        assert a.tobytes() == np.broadcast_to(a[:1], a.shape).tobytes(), key
+
+
+@pytest.mark.parametrize("copies", [60, 100, 250])
+def test_served_parts_where_their_scratch_ends(B, copies):
+    # 16.7 million floats of scratch: 3 ligands of up to 128 atoms at 1,024 orientations go from a
+    # part per chunk to fewer
+    p = S.make_pocket("small")
+    s = S.SearchSettings(1024, 8, 1, 1)
+    ligs = ligands([128, 100, 64], 2, p.channels)
+    one = run(B, [p], S.batch_from_ligands(ligs), s, orient=False)
+    batch = S.batch_from_ligands(ligs * copies)
+    A = int(batch.atom_offset[-1])
+    print("served copies %d" % copies, flush=True)
+    pid = B.exs_load_pocket_grid(p.values, p.spacing, p.origin)
+    srv = B.exs_server_create([pid], B.search_params(s.n_orient, s.torsion_steps, s.passes, s.n_offsets))
+    try:
+        out = B.exs_server_poll(srv, B.exs_server_submit(srv, batch, pocket_ids=[pid]), batch.n_ligands, A)
+    finally:
+        B.exs_server_destroy(srv)
+        B.exs_unload_pocket(pid)
+    for l in range(3):
+        assert (out["best_score"][l::3] == one["best_score"][l]).all()
+        assert (out["desc"]["orient"][l::3] == one["best"]["orient"][l]).all()
+    assert np.array_equal(out["coords"].reshape(copies, -1, 3), np.broadcast_to(one["coords"], (copies,) + one["coords"].shape))
