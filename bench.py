@@ -811,7 +811,7 @@ def method_steps_leg(B, torch, S, pid, s, stream, n=3000):
 def driver_legs(args, torch, S, B):
     """The rest of the headline metric, under the same run: the batched workload (100,000
     ligands over 15 resident pockets) as one persistent launch in a hipGraph, FP32 and with
-    16-bit texels + FP64 top-8 rescoring, beside the plain FP32 one-launch-per-pocket form, with
+    16-bit texels + FP64 top-8 rescoring, beside the plain FP32 form, with
     top-1 % hit overlap against the FP64 oracle's best scores of the first 20,000 ligands; and
     the serving workload (Poisson arrivals at 0.7 x capacity), FP32 and BF16 + top-8, against
     one plain launch per request from several workers."""
@@ -849,7 +849,7 @@ def driver_legs(args, torch, S, B):
         leg = {"docks_per_s": round(v, 1), "ms_per_step": round(step_s * 1e3, 3),
                "kernel_ms": round(kms, 3), "texels": ("f32", "bf16", "f16")[storage],
                "top_k_fp64": top_k,
-               "launch": "one launch per pocket" if not flags else "persistent + hipGraph"}
+               "launch": "one plain launch" if not flags else "persistent + hipGraph"}
         if flags:
             leg["roofline"] = roofline_of(B, batch, s, 8, kms, storage, sample_every=max(1, L // 10000))
         if golden is not None and L >= len(golden["best_score"]):
@@ -1098,7 +1098,7 @@ def main():
                         "orientations, S=%d torsion steps, P=%d passes, T=%d offsets; %s" % (
                             wl.name, L, pocket.n, pocket.channels, pocket.spacing, args.storage,
                             s.n_orient, s.torsion_steps, s.passes, s.n_offsets,
-                            "one persistent launch" if args.persistent else "one launch per pocket"),
+                            "one persistent launch" if args.persistent else "one plain launch"),
             "ligands": L, "atoms": A, "parallelism": "single GPU",
             "poses_per_lane": args.ppl, "ligands_per_wg": args.lpw,
             "rank_keep": args.rank_keep, "cluster_rmsd_A": args.cluster_rmsd if args.rank_keep else None,
