@@ -8,20 +8,22 @@ hipError_t launch_dock_f32(const DockArgs& a, int lanes, dim3 grid, dim3 block, 
                            hipStream_t st) {
 #define EXS_LAUNCH(SS, GG) \
     if (a.S == SS && lanes == GG) { \
-        hipLaunchKernelGGL((dock_kernel<SS, GG, TexF32>), grid, block, lds, st, a); \
+        hipLaunchKernelGGL((dock_kernel<SS, (GG < SS ? GG : SS), TexF32, (GG > SS)>), grid, block, lds, st, a); \
         return hipGetLastError(); \
     }
     EXS_LAUNCH(8, 4) EXS_LAUNCH(8, 8) EXS_LAUNCH(16, 4) EXS_LAUNCH(16, 8) EXS_LAUNCH(16, 16)
     EXS_LAUNCH(32, 4) EXS_LAUNCH(32, 8) EXS_LAUNCH(32, 16) EXS_LAUNCH(32, 32)
+    EXS_LAUNCH(8, 16) EXS_LAUNCH(16, 32) EXS_LAUNCH(32, 64)
 #undef EXS_LAUNCH
     return hipErrorInvalidValue;
 }
 
 const void* dock_kernel_fn_f32(int S, int lanes) {
 #define EXS_FN(SS, GG) \
-    if (S == SS && lanes == GG) return reinterpret_cast<const void*>(&dock_kernel<SS, GG, TexF32>);
+    if (S == SS && lanes == GG) return reinterpret_cast<const void*>(&dock_kernel<SS, (GG < SS ? GG : SS), TexF32, (GG > SS)>);
     EXS_FN(8, 4) EXS_FN(8, 8) EXS_FN(16, 4) EXS_FN(16, 8) EXS_FN(16, 16)
     EXS_FN(32, 4) EXS_FN(32, 8) EXS_FN(32, 16) EXS_FN(32, 32)
+    EXS_FN(8, 16) EXS_FN(16, 32) EXS_FN(32, 64)
 #undef EXS_FN
     return nullptr;
 }

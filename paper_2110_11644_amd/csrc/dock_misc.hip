@@ -75,9 +75,9 @@ hipError_t launch_dock(const DockArgs& a, int storage, const DockShape& sh, int 
     const dim3 grid(n_blocks), block(sh.waves * kWave);
     const size_t lds = (size_t)sh.lds.total;
     switch (storage) {
-        case 0: return launch_dock_f32(a, sh.lanes, grid, block, lds, st);
-        case 1: return launch_dock_bf16(a, sh.lanes, grid, block, lds, st);
-        case 2: return launch_dock_f16(a, sh.lanes, grid, block, lds, st);
+        case 0: return launch_dock_f32(a, sh.pair ? 2 * sh.lanes : sh.lanes, grid, block, lds, st);
+        case 1: return launch_dock_bf16(a, sh.pair ? 2 * sh.lanes : sh.lanes, grid, block, lds, st);
+        case 2: return launch_dock_f16(a, sh.pair ? 2 * sh.lanes : sh.lanes, grid, block, lds, st);
         default: return hipErrorInvalidValue;
     }
 }

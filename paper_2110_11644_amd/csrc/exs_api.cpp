@@ -247,7 +247,7 @@ int device_cus(int dev) {
     return g_dev[dev].cus;
 }
 int resident_workgroups(int dev, int storage, int S, const DockShape& sh, int* out) {
-    const void* fn = dock_kernel_fn(storage, S, sh.lanes);
+    const void* fn = dock_kernel_fn(storage, S, sh.pair ? 2 * sh.lanes : sh.lanes);
     if (!fn) return fail(EXS_EINVAL, "no kernel for this configuration");
     if (sh.lds.total > 64 * 1024)
         HIP_TRY(hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, sh.lds.total));
@@ -308,7 +308,8 @@ static double lane_cost(int lanes, int S) {
 // launch that shares the chip, which count in the rounds (a served burst in shapes for each iteration
 // alone: 5.8 ms, 4.2 with the other's).
 constexpr double kAloneRounds = 2.2;
-DockShape dock_shape(int n_lig, int beside, int n_max, int rot_max, int K, int S, int top_k, int lpw, int ppl, int cus) {
+constexpr int kPairChunks = 6;   // chunks a CU up to which two waves share one
+DockShape dock_shape(int n_lig, int beside, int64_t n_atoms, int n_max, int rot_max, int K, int S, int top_k, int lpw, int ppl, int cus) {
     const int64_t n_cu = std::max(1, cus);
     auto chunks_of = [&](int lanes) { return (K * lanes + kWave - 1) / kWave; };
     auto lds_of = [&](int w, int lanes) { return dock_lds(lpw, n_max, rot_max, top_k, w, lanes, S); };
@@ -350,6 +351,18 @@ DockShape dock_shape(int n_lig, int beside, int n_max, int rot_max, int K, int S
             sh.parts = (chunks + sh.waves * each - 1) / (sh.waves * each);
         }
         best = sh;
+    }
+    // A turn a lane and most of the chip idle: a second wave counts the clashes while the first looks
+    // up.  One ligand of 38 atoms 110 -> 87 us, 4 of up to 60 106 -> 85, 16: 197 -> 168; 16-bit, up to
+    // 90 atoms, 13: 233 -> 187, 20: 360 -> 263, 32: 291 -> 303; 64 of 24 atoms at 64 orientations of 16
+    // turns 59 -> 49, 100 of them 60 -> 68.  The line is where the pairs, six a CU, are all resident,
+    // with smaller ligands counted by their atoms, for they make room soon.
+    const double full = beside + (double)n_atoms / std::max(1, n_max);
+    if (best.lanes == S && lpw == 1 && ppl == 1 && full * chunks_of(S) <= kPairChunks * n_cu &&
+        lds_of(2, S).total <= kDockLdsBytes) {
+        best.pair = true;
+        best.waves = 2;
+        best.parts = chunks_of(S);
     }
     best.lds = lds_of(best.waves, best.lanes);
     return best;
@@ -991,7 +1004,7 @@ void base_args(DockArgs& a, const Batch& b, const exs_search_params& p, const La
 // The launch of `count` ligands of batch b, from position `start` of the order.
 int plan_launch(const Batch& b, const exs_search_params& p, const LaunchSettings& ls, int dev, int storage,
                 int start, int count, bool persistent, DockLaunch* out) {
-    out->shape = dock_shape(count, 0, b.n_max, b.rot_max, p.n_orient, p.torsion_steps, ls.top_k, ls.lpw, ls.ppl,
+    out->shape = dock_shape(count, 0, b.L > 0 ? (int64_t)b.A * count / b.L : 0, b.n_max, b.rot_max, p.n_orient, p.torsion_steps, ls.top_k, ls.lpw, ls.ppl,
                             rt::device_cus(dev));
     out->storage = storage;
     out->start = start;

@@ -166,10 +166,11 @@ constexpr int kSlotHead = 4 + kMaxRot;
 // Shape of a dock launch: lanes per orientation, waves of a workgroup, workgroups per ligand.
 struct DockShape {
     int lanes = 4, waves = 1, parts = 1;
+    bool pair = false;   // two waves search the same orientations: one looks up, one counts clashes
     DockLds lds{};
     int64_t slot_floats(int lpw, int n_max) const { return kSlotHead + ((int64_t)lpw * waves + (parts > 1 ? 1 : 0)) * 3 * n_max; }
 };
-DockShape dock_shape(int n_lig, int beside, int n_max, int rot_max, int K, int S, int top_k, int lpw, int ppl, int cus);
+DockShape dock_shape(int n_lig, int beside, int64_t n_atoms, int n_max, int rot_max, int K, int S, int top_k, int lpw, int ppl, int cus);
 
 // Everything one dock launch reads and writes.
 struct DockArgs {

@@ -34,6 +34,7 @@
 #include <map>
 #include <memory>
 #include <mutex>
+#include <numeric>
 #include <string>
 #include <thread>
 #include <unordered_map>
@@ -577,7 +578,7 @@ bool Server::launch(Iteration& it) {
     for (int i = 0; i < n_iters_; ++i)
         if (it_[i].running) beside += it_[i].n_lig;
     it.n_lig = n;
-    DockShape sh = dock_shape(n, beside, n_max, rot_max, K_, prm_.torsion_steps, top_k_, lpw_, ppl_, rt::device_cus(dev_));
+    DockShape sh = dock_shape(n, beside, std::accumulate(nat.begin(), nat.end(), (int64_t)0), n_max, rot_max, K_, prm_.torsion_steps, top_k_, lpw_, ppl_, rt::device_cus(dev_));
     if (sh.parts > 1)   // a scratch slot per part: as many parts as fit; at one, a slot per workgroup
         sh.parts = (int)std::max<int64_t>(1, std::min<int64_t>(sh.parts, scratch_floats_ / (n * sh.slot_floats(lpw_, n_max))));
     a.lds = sh.lds;

@@ -121,3 +121,18 @@ def test_served_parts_where_their_scratch_ends(B, copies):
         assert (out["best_score"][l::3] == one["best_score"][l]).all()
         assert (out["desc"]["orient"][l::3] == one["best"]["orient"][l]).all()
     assert np.array_equal(out["coords"].reshape(copies, -1, 3), np.broadcast_to(one["coords"], (copies,) + one["coords"].shape))
+
+
+@pytest.mark.parametrize("steps,passes,rot", [(32, 0, 3), (32, 2, 0), (16, 3, 4), (8, 2, 1)])
+def test_two_waves_a_chunk_without_bonds_or_passes(B, oracle_lib, steps, passes, rot):
+    # few ligands: a second wave counts the clashes; many: one wave does everything
+    p = S.make_pocket("small")
+    s = S.SearchSettings(40, steps, passes, 27)
+    ligs = ligands([6, 30, 70], rot, p.channels)
+    print("two waves S %d P %d rot %d" % (steps, passes, rot), flush=True)
+    one = run(B, [p], S.batch_from_ligands(ligs), s)
+    check(oracle_lib, oracle_lib.Grid.of(p), s, S.batch_from_ligands(ligs), one, len(ligs))
+    many = run(B, [p], S.batch_from_ligands(ligs * 900), s)
+    for l in range(2700):
+        assert many["score"][l].tobytes() == one["score"][l % 3].tobytes(), l
+        assert many["desc"][l].tobytes() == one["desc"][l % 3].tobytes(), l
