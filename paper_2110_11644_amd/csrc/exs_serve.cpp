@@ -279,8 +279,8 @@ int Server::create(const int32_t* pockets, int n_pockets, const exs_search_param
     max_iter_ = cfg.max_iter_ligands > 0 ? cfg.max_iter_ligands : 4 * wgs * lpw_;
     // budget: scratch for the iterations first, the rest is the request arena
     const int64_t slot_floats = (int64_t)lpw_ * EXS_MAX_ATOMS * 3 * (wpl_ * kWave * ppl_);
-    // what is allocated of it: the waves' best poses take a small part (64 MB hold 43,000 of the
-    // largest ligands'; a launch that splits its ligands further than that is not split)
+    // what is allocated of it: the parts' and waves' best poses take a small part (64 MB hold 20,000 parts
+    // of the largest ligands; a launch that would split its ligands further splits them into fewer)
     scratch_floats_ = std::min<int64_t>(wgs * slot_floats, (int64_t)1 << 24);
     res_rec_bytes_ = sizeof(ResultRec) * (size_t)max_iter_;
     res_coord_bytes_ = sizeof(float) * 3 * (size_t)EXS_MAX_ATOMS * max_iter_;
