@@ -85,20 +85,30 @@ extern "C" int exs_dock_batch_noalloc(int64_t batch, const exs_search_params* pa
                         "batch needs %zu B of per-orientation results and %zu B per workgroup of "
                         "pose scratch; the no-allocation buffer holds %zu B (split the batch)",
                         c.used, (size_t)pl.limit_bytes, kScratchBytes);
-    // the rest takes less than limit_bytes for one workgroup: the order of the orientations, the
-    // finished-part counters (a launch that splits its ligands) and the scratch slots
+    // the orientations' order and one workgroup's scratch take less than limit_bytes.  Ligands are split
+    // into as many parts as the buffer holds a slot of, beside the finished-part counters; where that
+    // is less than two each (many tiny ligands near the limit), they stay whole: no counters, a slot
+    // per workgroup
     int32_t* order_k = c.take<int32_t>((size_t)K);
     a.order_k = order_k;
+    DockShape sh = pl.shape;
+    if (sh.parts > 1) {
+        Carve with = c;
+        int32_t* counters = with.take<int32_t>(kMaxWorkQueues + (size_t)L);   // the queue's beside them
+        const int64_t room = (int64_t)kScratchBytes - (int64_t)with.used;
+        const int64_t slot = sh.slot_floats(a.lpw, a.n_max) * (int64_t)sizeof(float);
+        sh.parts = (int)std::max<int64_t>(1, std::min<int64_t>(sh.parts, std::max<int64_t>(0, room) / slot / L));
+        if (sh.parts > 1) {
+            c = with;
+            a.tile_counter = counters;
+            a.done = counters + kMaxWorkQueues;
+        }
+    }
+    a.parts = sh.parts;
+    a.slot_floats = sh.slot_floats(a.lpw, a.n_max);
+    a.n_tiles = (int)((L + a.lpw - 1) / a.lpw) * a.parts;
     const size_t slot_bytes = (size_t)a.slot_floats * sizeof(float);
-    if (a.parts > 1) {   // the counters side by side
-        a.tile_counter = c.take<int32_t>(kMaxWorkQueues + (size_t)L);
-        a.done = a.tile_counter + kMaxWorkQueues;
-    }
     const int64_t fit = std::max<int64_t>(0, (int64_t)kScratchBytes - (int64_t)c.used) / (int64_t)slot_bytes;
-    if (a.parts > 1 && fit < pl.slots) {   // a slot per part: as many parts as fit; at one, a slot per workgroup
-        a.parts = (int)std::max<int64_t>(1, fit / L);
-        a.n_tiles = (int)((L + a.lpw - 1) / a.lpw) * a.parts;
-    }
     if (fit < 1) return rt::fail(EXS_EINVAL, "the no-allocation buffer does not hold a workgroup's scratch (split the batch)");
     const int blocks = (int)std::min<int64_t>({(int64_t)pl.blocks, fit, (int64_t)a.n_tiles});
     a.scratch = c.take<float>((size_t)(a.parts > 1 ? a.n_tiles : blocks) * a.slot_floats);
@@ -112,7 +122,7 @@ extern "C" int exs_dock_batch_noalloc(int64_t batch, const exs_search_params* pa
     // single ligand's 150 us
     hipError_t e = launch_orientation_table((int)K, rot32, nullptr, order_k, a.tile_counter,
                                             kMaxWorkQueues + (a.parts > 1 ? (int)L : 0), st);
-    if (e == hipSuccess) e = launch_dock(a, pl.storage, pl.shape, blocks, st);
+    if (e == hipSuccess) e = launch_dock(a, pl.storage, sh, blocks, st);
     if (e != hipSuccess) return rt::fail(EXS_EDEVICE, "no-allocation launch: %s", hipGetErrorString(e));
     return EXS_OK;
 }
