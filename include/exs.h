@@ -236,10 +236,10 @@ int exs_pack_topology(int n, const float* x, const float* y, const float* z, con
  *                  closer than the cutoff
  *   top_k          0, or 1..EXS_MAX_TOPK: rescore each ligand's top_k poses in
  *                  FP64 from the FP32 master grid and pick the best by FP64
- *   poses_per_lane 0 = auto, or 1, 2, 4: share of a ligand's orientations that one wave
- *                  searches (1: the least, a workgroup has the most waves; the results are
- *                  the same)
- *   ligands_per_wg 0 = auto, or 1, 2, 4, 8 (ligands per workgroup)
+ *   poses_per_lane 0 = auto, or 1, 2, 4, and ligands_per_wg 0 = auto, or 1, 2, 4, 8: tile
+ *                  sizes.  The launch takes the shape that suits its ligands whatever they
+ *                  are, with the same results; they only enter the sizes that the
+ *                  no-allocation buffer and a server's budget are held to
  *   flags          EXS_FLAG_* bits
  *   cluster_rmsd_A, rank_keep   ranking of each ligand's K final poses (Sec. 3.1,
  *                  third step), when rank_keep > 0: poses by score (lower

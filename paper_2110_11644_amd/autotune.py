@@ -21,10 +21,8 @@ LPW_CHOICES = (1, 2, 4, 8)
 
 
 def candidate_tiles(n_orient: int) -> List[Tuple[int, int]]:
-    """Every (poses per lane, ligands per workgroup) of {1, 2, 4} x {1, 2, 4, 8}: the library
-    fits any of them in a workgroup (its waves take a tile's orientation chunks in turn when
-    the tile has more chunks than the workgroup has waves) and refuses one only when a single
-    wave's LDS does not fit, which tune() then skips."""
+    """Every (poses per lane, ligands per workgroup) of {1, 2, 4} x {1, 2, 4, 8}.  The library
+    takes any of them and chooses the launch's shape by its ligands, so they run alike."""
     return [(ppl, lpw) for ppl in PPL_CHOICES for lpw in LPW_CHOICES]
 
 

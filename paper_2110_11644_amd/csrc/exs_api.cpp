@@ -309,17 +309,17 @@ static double lane_cost(int lanes, int S) {
 // alone: 5.8 ms, 4.2 with the other's).
 constexpr double kAloneRounds = 2.2;
 constexpr int kPairChunks = 6;   // chunks a CU up to which two waves share one
-DockShape dock_shape(int n_lig, int beside, int64_t n_atoms, int n_max, int rot_max, int K, int S, int top_k, int lpw, int ppl, int cus) {
+DockShape dock_shape(int n_lig, int beside, int64_t n_atoms, int n_max, int rot_max, int K, int S, int top_k, int cus) {
     const int64_t n_cu = std::max(1, cus);
     auto chunks_of = [&](int lanes) { return (K * lanes + kWave - 1) / kWave; };
-    auto lds_of = [&](int w, int lanes) { return dock_lds(lpw, n_max, rot_max, top_k, w, lanes, S); };
+    auto lds_of = [&](int w, int lanes) { return dock_lds(n_max, rot_max, top_k, w, lanes, S); };
     DockShape best;
     double best_time = -1.0;
     for (int lanes : {4, 8, 16, 32}) {
         if (lanes > S) continue;
         DockShape sh;
         sh.lanes = lanes;
-        const int chunks = chunks_of(lanes), items = lpw * chunks;
+        const int chunks = chunks_of(lanes);
         const int64_t total = (int64_t)n_lig * chunks;
         // the workgroup size with the most waves on a CU; one workgroup alone on a CU leaves it idle
         // while it stages and finishes; 5 to 7 waves spread unevenly over the four SIMDs, and a second
@@ -332,24 +332,22 @@ DockShape dock_shape(int n_lig, int beside, int64_t n_atoms, int n_max, int rot_
         int on_cu = 1;
         for (int w : {1, 2, 3, 4, 8}) {
             const int lds = lds_of(w, lanes).total;
-            if (w > items || lds > kDockLdsBytes) break;
+            if (w > chunks || lds > kDockLdsBytes) break;
             const int fit = dock_waves_per_cu(lds, w);
-            const double wait = top_k > 0 || lpw > 1 ? 1.0 : 1.0 - 0.012 * (w - 1);
-            const double score = (double)items / (double)((items + w - 1) / w * w) * fit * (fit == w ? 0.8 : 1.0) * wait;
+            const double wait = top_k > 0 ? 1.0 : 1.0 - 0.012 * (w - 1);
+            const double score = (double)chunks / (double)((chunks + w - 1) / w * w) * fit * (fit == w ? 0.8 : 1.0) * wait;
             if (score >= most) { most = score; sh.waves = w; on_cu = fit; }
         }
         // few chunks: spread over the CUs first
-        if (lpw == 1 && total <= 4 * n_cu) sh.waves = std::min(sh.waves, total <= 2 * n_cu ? 1 : 2);
-        sh.waves = std::max(1, sh.waves / ppl);
+        if (total <= 4 * n_cu) sh.waves = std::min(sh.waves, total <= 2 * n_cu ? 1 : 2);
         const double rounds = (double)(n_lig + beside) * chunks / (double)(n_cu * std::max(1, on_cu));
         const double time = lane_cost(lanes, S) / lanes * std::max(on_cu, 11) *
                             std::pow(std::pow(rounds, 4.0) + std::pow(kAloneRounds, 4.0), 0.25);
         if (best_time >= 0.0 && time >= best_time) continue;
         best_time = time;
-        if (lpw == 1) {   // a wave takes a few chunks one after another, fewer than a tenth of the rounds
-            const int each = std::max(1, (int)std::min<double>(rounds / 10.0, chunks));
-            sh.parts = (chunks + sh.waves * each - 1) / (sh.waves * each);
-        }
+        // a wave takes a few chunks one after another, fewer than a tenth of the rounds
+        const int each = std::max(1, (int)std::min<double>(rounds / 10.0, chunks));
+        sh.parts = (chunks + sh.waves * each - 1) / (sh.waves * each);
         best = sh;
     }
     // A turn a lane and most of the chip idle: a second wave counts the clashes while the first looks
@@ -358,7 +356,7 @@ DockShape dock_shape(int n_lig, int beside, int64_t n_atoms, int n_max, int rot_
     // turns 59 -> 49, 100 of them 60 -> 68.  The line is where the pairs, six a CU, are all resident,
     // with smaller ligands counted by their atoms, for they make room soon.
     const double full = beside + (double)n_atoms / std::max(1, n_max);
-    if (best.lanes == S && lpw == 1 && ppl == 1 && full * chunks_of(S) <= kPairChunks * n_cu &&
+    if (best.lanes == S && full * chunks_of(S) <= kPairChunks * n_cu &&
         lds_of(2, S).total <= kDockLdsBytes) {
         best.pair = true;
         best.waves = 2;
@@ -918,8 +916,8 @@ hipError_t enqueue_dock(const DockArgs& base, const Batch& b, const std::vector<
         a.n_order = d.count;
         a.lds = d.shape.lds;
         a.parts = d.shape.parts;
-        a.slot_floats = d.shape.slot_floats(a.lpw, a.n_max);
-        a.n_tiles = (d.count + a.lpw - 1) / a.lpw * a.parts;
+        a.slot_floats = d.shape.slot_floats(a.n_max);
+        a.n_tiles = d.count * a.parts;
         a.persistent = persistent ? 1 : 0;
         if (persistent) {
             a.queue_bounds = d_order + b.L;
@@ -937,7 +935,7 @@ hipError_t enqueue_dock(const DockArgs& base, const Batch& b, const std::vector<
 
 // Validated search settings of a batch.
 struct LaunchSettings {
-    int ppl = 1, lpw = 1, top_k = 0, storage = 0;
+    int ppl = 1, lpw = 1, top_k = 0, storage = 0;   // ppl, lpw: checked, and part of keys and limits
 };
 
 int launch_settings(const Batch& b, const exs_search_params& p, bool persistent, LaunchSettings* out) {
@@ -991,7 +989,7 @@ void base_args(DockArgs& a, const Batch& b, const exs_search_params& p, const La
     a.step64 = (double)p.offset_step_A;
     a.cut2_64 = (double)p.clash_cutoff_A * (double)p.clash_cutoff_A;
     a.pen64 = (double)p.clash_penalty;
-    a.top_k = ls.top_k; a.lpw = ls.lpw;
+    a.top_k = ls.top_k;
     a.rank_keep = p.rank_keep;
     a.rank_thr2 = p.cluster_rmsd_A * p.cluster_rmsd_A;
     a.n_max = b.n_max;
@@ -1004,12 +1002,11 @@ void base_args(DockArgs& a, const Batch& b, const exs_search_params& p, const La
 // The launch of `count` ligands of batch b, from position `start` of the order.
 int plan_launch(const Batch& b, const exs_search_params& p, const LaunchSettings& ls, int dev, int storage,
                 int start, int count, bool persistent, DockLaunch* out) {
-    out->shape = dock_shape(count, 0, b.L > 0 ? (int64_t)b.A * count / b.L : 0, b.n_max, b.rot_max, p.n_orient, p.torsion_steps, ls.top_k, ls.lpw, ls.ppl,
-                            rt::device_cus(dev));
+    out->shape = dock_shape(count, 0, b.L > 0 ? (int64_t)b.A * count / b.L : 0, b.n_max, b.rot_max, p.n_orient, p.torsion_steps, ls.top_k, rt::device_cus(dev));
     out->storage = storage;
     out->start = start;
     out->count = count;
-    out->blocks = (count + ls.lpw - 1) / ls.lpw * out->shape.parts;
+    out->blocks = count * out->shape.parts;
     out->slots = out->blocks;
     int resident = 0;
     if (int rc = rt::resident_workgroups(dev, storage, p.torsion_steps, out->shape, &resident)) return rc;
@@ -1064,7 +1061,7 @@ int exs_dock_batch(int64_t batch, const exs_search_params* params, void* stream,
             if (count == 0) continue;
             DockLaunch d;
             if (int rc = plan_launch(*b, p, ls, dev, st_g, start, count, persistent, &d)) return rc;
-            scratch_floats = std::max(scratch_floats, d.slots * d.shape.slot_floats(lpw, b->n_max));
+            scratch_floats = std::max(scratch_floats, d.slots * d.shape.slot_floats(b->n_max));
             launches.push_back(d);
             start += count;
         }
@@ -1460,8 +1457,8 @@ int noalloc_plan(int64_t batch, const exs_search_params* params, NoAllocPlan* ou
     a.n_order = b->L;
     a.lds = d.shape.lds;
     a.parts = d.shape.parts;
-    a.slot_floats = d.shape.slot_floats(a.lpw, a.n_max);
-    a.n_tiles = (b->L + a.lpw - 1) / a.lpw * a.parts;
+    a.slot_floats = d.shape.slot_floats(a.n_max);
+    a.n_tiles = b->L * a.parts;
     a.persistent = 1;
     a.queue_bounds = nullptr;
     a.n_queues = 1;

@@ -10,7 +10,6 @@ constexpr int kWave = 64;
 constexpr int kMaxAtoms = 128;   // bits of one exclusion / moving mask row
 constexpr int kMaxRot = 32;
 constexpr int kMaxTopK = 32;
-constexpr int kMaxLpw = 8;       // ligands per workgroup
 constexpr int kMaxWavesPerWg = 8;
 constexpr int kMaxThreadsPerWg = kMaxWavesPerWg * kWave;
 constexpr int kXcds = 8;   // accelerator complex dies of an MI355X, each with its own L2
@@ -117,23 +116,22 @@ struct ResultRec {
     double score64;
 };
 
-// Dynamic LDS of a dock workgroup (byte offsets): the turn table, per ligand of the tile its
-// topology (ref .. topk relative to the ligand's slot), the waves' best (score, orientation) per
-// ligand, and per wave its poses, clash difference arrays, queue of crossing pairs and torsions
+// Dynamic LDS of a dock workgroup (byte offsets): the turn table, the ligand's topology (ref ..
+// topk relative to lig), the waves' best (score, orientation), and per wave its poses, clash difference arrays, queue of crossing pairs and torsions
 // (diff, queue, theta relative to the wave's part).  Sized by the launch's largest ligand: LDS decides how many waves fit on a CU.
 struct DockLds {
-    int32_t ligs, lig_bytes;
+    int32_t lig;
     int32_t ref, excl, rmask, ruv, mc, perm, perm_stride, e64, topk;
     int32_t rec;
     int32_t waves, wave_bytes, diff, queue, theta;
     int32_t total;
 };
 __host__ __device__ inline int lds_align(int x) { return (x + 15) & ~15; }
-inline DockLds dock_lds(int lpw, int n_max, int rot_max, int top_k, int waves, int lanes, int S) {
+inline DockLds dock_lds(int n_max, int rot_max, int top_k, int waves, int lanes, int S) {
     DockLds d;
     const int no = kWave / lanes;
     int at = lds_align(2 * S * 4);
-    d.ligs = at;
+    d.lig = at;
     int p = 32;                                   // lig, n, nrot, pocket, atom_base, rot_base
     d.ref = p; p += 16 * n_max;
     d.excl = p; p += 16 * n_max;
@@ -145,9 +143,8 @@ inline DockLds dock_lds(int lpw, int n_max, int rot_max, int top_k, int waves, i
     d.perm = p;
     d.perm_stride = (n_max + 3) & ~3;
     p += lds_align(d.perm_stride * rot_max);
-    d.lig_bytes = p;
-    at += lpw * d.lig_bytes;
-    d.rec = at; at += lds_align(8 * lpw * waves);
+    at += p;
+    d.rec = at; at += lds_align(8 * waves);
     d.waves = at;
     p = lds_align(12 * n_max * no);               // the poses (the FP64 ones of the top_k, 24 n_max, fit)
     d.diff = p; p += lds_align(2 * S * no);
@@ -168,9 +165,9 @@ struct DockShape {
     int lanes = 4, waves = 1, parts = 1;
     bool pair = false;   // two waves search the same orientations: one looks up, one counts clashes
     DockLds lds{};
-    int64_t slot_floats(int lpw, int n_max) const { return kSlotHead + ((int64_t)lpw * waves + (parts > 1 ? 1 : 0)) * 3 * n_max; }
+    int64_t slot_floats(int n_max) const { return kSlotHead + ((int64_t)waves + (parts > 1 ? 1 : 0)) * 3 * n_max; }
 };
-DockShape dock_shape(int n_lig, int beside, int64_t n_atoms, int n_max, int rot_max, int K, int S, int top_k, int lpw, int ppl, int cus);
+DockShape dock_shape(int n_lig, int beside, int64_t n_atoms, int n_max, int rot_max, int K, int S, int top_k, int cus);
 
 // Everything one dock launch reads and writes.
 struct DockArgs {
@@ -183,7 +180,7 @@ struct DockArgs {
     const uint4* rot_mask;    // [R] atoms that turn with the bond
     const int32_t* order;     // ligands in processing order (pocket-major, longest first within)
     int32_t n_order;          // ligands in this launch
-    int32_t n_tiles;          // workgroups' worth of work: ceil(n_order / lpw), times parts
+    int32_t n_tiles;          // workgroups' worth of work: n_order times parts
     // pockets
     const GridDesc* grids;
     // search settings
@@ -194,13 +191,12 @@ struct DockArgs {
     float step, cut2, pen, pad0;
     double step64, cut2_64, pen64;
     int32_t top_k;
-    int32_t lpw;              // ligands per workgroup
-    int32_t parts;            // workgroups that share a ligand's chunks (> 1: lpw = 1)
+    int32_t parts;            // workgroups that share a ligand's chunks
     int32_t n_max;            // atoms of the largest ligand in the launch
     int32_t persistent;
     DockLds lds;
     // scratch slots, one per workgroup (parts > 1: one per tile): kSlotHead words, with parts > 1
-    // the part's pose [n_max][3], then [lpw][waves][n_max][3]
+    // the part's pose [n_max][3], then [waves][n_max][3]
     float* scratch;
     int64_t slot_floats;
     int32_t* tile_counter;    // persistent launches: next tile of each queue [n_queues]

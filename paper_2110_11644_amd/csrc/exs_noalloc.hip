@@ -96,7 +96,7 @@ extern "C" int exs_dock_batch_noalloc(int64_t batch, const exs_search_params* pa
         Carve with = c;
         int32_t* counters = with.take<int32_t>(kMaxWorkQueues + (size_t)L);   // the queue's beside them
         const int64_t room = (int64_t)kScratchBytes - (int64_t)with.used;
-        const int64_t slot = sh.slot_floats(a.lpw, a.n_max) * (int64_t)sizeof(float);
+        const int64_t slot = sh.slot_floats(a.n_max) * (int64_t)sizeof(float);
         sh.parts = (int)std::max<int64_t>(1, std::min<int64_t>(sh.parts, std::max<int64_t>(0, room) / slot / L));
         if (sh.parts > 1) {
             c = with;
@@ -105,8 +105,8 @@ extern "C" int exs_dock_batch_noalloc(int64_t batch, const exs_search_params* pa
         }
     }
     a.parts = sh.parts;
-    a.slot_floats = sh.slot_floats(a.lpw, a.n_max);
-    a.n_tiles = (int)((L + a.lpw - 1) / a.lpw) * a.parts;
+    a.slot_floats = sh.slot_floats(a.n_max);
+    a.n_tiles = (int)L * a.parts;
     const size_t slot_bytes = (size_t)a.slot_floats * sizeof(float);
     const int64_t fit = std::max<int64_t>(0, (int64_t)kScratchBytes - (int64_t)c.used) / (int64_t)slot_bytes;
     if (fit < 1) return rt::fail(EXS_EINVAL, "the no-allocation buffer does not hold a workgroup's scratch (split the batch)");

@@ -350,7 +350,7 @@ int Server::create(const int32_t* pockets, int n_pockets, const exs_search_param
     a.step = p.offset_step_A; a.cut2 = p.clash_cutoff_A * p.clash_cutoff_A; a.pen = p.clash_penalty;
     a.step64 = p.offset_step_A; a.cut2_64 = (double)p.clash_cutoff_A * p.clash_cutoff_A;
     a.pen64 = p.clash_penalty;
-    a.top_k = top_k_; a.lpw = lpw_;
+    a.top_k = top_k_;
     a.persistent = 1;
     // the streams get a hardware queue each, several ms apiece: created on threads of their own
     {
@@ -578,14 +578,14 @@ bool Server::launch(Iteration& it) {
     for (int i = 0; i < n_iters_; ++i)
         if (it_[i].running) beside += it_[i].n_lig;
     it.n_lig = n;
-    DockShape sh = dock_shape(n, beside, std::accumulate(nat.begin(), nat.end(), (int64_t)0), n_max, rot_max, K_, prm_.torsion_steps, top_k_, lpw_, ppl_, rt::device_cus(dev_));
+    DockShape sh = dock_shape(n, beside, std::accumulate(nat.begin(), nat.end(), (int64_t)0), n_max, rot_max, K_, prm_.torsion_steps, top_k_, rt::device_cus(dev_));
     if (sh.parts > 1)   // a scratch slot per part: as many parts as fit; at one, a slot per workgroup
-        sh.parts = (int)std::max<int64_t>(1, std::min<int64_t>(sh.parts, scratch_floats_ / (n * sh.slot_floats(lpw_, n_max))));
+        sh.parts = (int)std::max<int64_t>(1, std::min<int64_t>(sh.parts, scratch_floats_ / (n * sh.slot_floats(n_max))));
     a.lds = sh.lds;
     a.parts = sh.parts;
     a.n_max = n_max;
-    a.slot_floats = sh.slot_floats(lpw_, n_max);
-    a.n_tiles = (a.n_order + lpw_ - 1) / lpw_ * sh.parts;
+    a.slot_floats = sh.slot_floats(n_max);
+    a.n_tiles = a.n_order * sh.parts;
     int resident = 1;
     if (rt::resident_workgroups(dev_, storage_, prm_.torsion_steps, sh, &resident) != EXS_OK) resident = 1;
     int64_t blocks = std::min(a.n_tiles, resident);
