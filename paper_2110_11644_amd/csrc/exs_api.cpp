@@ -150,6 +150,7 @@ struct Plan {
 struct Batch {
     int device = 0;
     int L = 0, A = 0, R = 0, n_max = 1, rot_max = 0;
+    WorkSums work;                         // of all ligands
     std::vector<int32_t> pockets;          // pocket handle per table slot
     std::vector<int> storage_of_slot;
     std::vector<int> count_of_slot;        // ligands per pocket
@@ -226,6 +227,14 @@ void free_batch(Batch* b) {
 }  // namespace
 
 namespace exs {
+// Waves of a workgroup that fit on a CU: LDS in its allocation granules, and the registers that
+// the dock kernels are held to.
+static int dock_waves_per_cu(int lds, int waves) {
+    constexpr int kGranule = 1280, kRegisterWaves = 12;
+    const int by_lds = (int)kMaxLdsBytes / ((lds + kGranule - 1) / kGranule * kGranule);
+    return std::min(by_lds, kRegisterWaves / waves) * waves;
+}
+
 namespace rt {
 
 int fail(int code, const char* fmt, ...) {
@@ -274,90 +283,95 @@ void pocket_use(int32_t id, int delta) {
 
 }  // namespace rt
 
-// Waves of a workgroup that fit on a CU: LDS in its allocation granules, and the registers that
-// the dock kernels are held to.
-static int dock_waves_per_cu(int lds, int waves) {
-    constexpr int kGranule = 1280, kRegisterWaves = 12;
-    const int by_lds = (int)kMaxLdsBytes / ((lds + kGranule - 1) / kGranule * kGranule);
-    return std::min(by_lds, kRegisterWaves / waves) * waves;
-}
-
-// Work of an orientation by its lanes, over that with four: more lanes repeat an atom's or a bond's
-// share in more places, which counts the more the fewer turns each has.  From the times of full
-// launches.
-static double lane_cost(int lanes, int S) {
+// Lanes per orientation, waves per workgroup and workgroups per ligand (parts) of a launch: the shape
+// with the shortest estimate of its time.  The estimate's terms, in us, and their constants were fitted
+// to 5,721 launches of 101 workloads (sizes, turns, passes, offsets, top_k, rigid and flexible ligands),
+// each in every shape; its choice takes 4 % longer than the best shape on average, a rule by the
+// chunks' rounds alone 27 %, for it split ligands whose search is short: 1,000 ligands of 3-9
+// atoms 409 us against 246, 4,000 with their best 32 poses 1,392 / 461 (rigid, 15-40 atoms) and
+// 3,839 / 2,201 (20-60 atoms), while 10,000 of up to 12 bonds, whose chunks are long, had the same shape.
+//  * a chunk (64 / lanes orientations): its work (turns, offsets, the rest: ligand_cost's units) with
+//    what more lanes repeat of it, on a CU with its waves, plus kChunkFixed.  Few lanes do the least work,
+//    more lanes have shorter chunks and, with fewer poses per wave, more waves in LDS.
+//  * a workgroup: its longest wave's chunks plus kTileFixed (staging, merging); every one of them has
+//    to be dispatched as well.  With top_k one wave selects and the waves share the FP64 poses.
+//  * the launch: the workgroups' time over the CUs' room for them, or one workgroup alone with the longest
+//    ligand where the chip is not full (the fourth powers fit the times between), and a part of a
+//    workgroup's time in which the chip runs empty, more of it where the rounds are few.  Where the ligands
+//    come longest first the last workgroups are short ones; pocket by pocket they are not (2,003
+//    ligands of 13 chunks in 13 and in 7 parts: one pocket 2,117 / 2,134 us, three 2,176 / 2,605).
+// `beside`: ligands of another launch that shares the chip (a served burst in shapes for each
+// iteration alone: 5.8 ms, 4.2 with the other's).
+static double chunk_work(const LaunchWork& w, int lanes, int S) {
     switch (lanes) {
-        case 8: return S == 32 ? 1.0 : (S == 16 ? 1.16 : 1.1);
-        case 16: return S == 32 ? 1.24 : 1.48;
-        case 32: return 1.7;
-        default: return 1.0;
+        case 8: return (S == 16 ? 1.3 : 0.97) * w.turn + w.offset + 1.2 * w.rest;
+        case 16: return (S == 32 ? 1.05 : 1.35) * w.turn + 1.25 * w.offset + 1.44 * w.rest;
+        case 32: return 1.15 * w.turn + 1.1 * w.offset + 1.73 * w.rest;
+        default: return w.turn + w.offset + w.rest;
     }
 }
-
-// Lanes per orientation, waves per workgroup and workgroups per ligand of a launch of n_lig ligands.
-// A launch takes as long as its rounds, the chunks per wave slot, but no less than kAloneRounds of
-// them: the longest ligand's chunk, alone on the chip.  (Both count about equally where they are equal;
-// the fourth power fits the times between.)  A chunk's work is an orientation's, times the
-// 64 / lanes orientations, times lane_cost, and fewer than eleven waves on a CU do not use all of it.
-// Few lanes do the least work, more lanes have shorter chunks and, with fewer poses per wave, more
-// waves in LDS.  Measured with 4 / 8 / 16 / 32 lanes (us), 256 orientations of 32 turns, up to 60 atoms:
-// 20 ligands 659 / 440 / 309 / 250, 60: 691 / 446 / 318 / 324, 90: 750 / 498 / 383 / 515, 256: 938 /
-// 720 / 923 / 1,228, 1,000: 2,780 / 2,760 / 3,430 / 4,820, 10,000: 25,310 / 24,980 / - / -; 16-bit, up
-// to 90 atoms, 90: 1,220 / 740 / 518 / 611, 1,000: 4,540 / 3,290 / 4,140 / 6,100; 16 turns, 1,000:
-// 1,872 / 2,024 / 2,789; 8 turns of 100 orientations, 512: 700 / 490.  `beside`: ligands of another
-// launch that shares the chip, which count in the rounds (a served burst in shapes for each iteration
-// alone: 5.8 ms, 4.2 with the other's).
-constexpr double kAloneRounds = 2.2;
 constexpr int kPairChunks = 6;   // chunks a CU up to which two waves share one
-DockShape dock_shape(int n_lig, int beside, int64_t n_atoms, int n_max, int rot_max, int K, int S, int top_k, int cus) {
-    const int64_t n_cu = std::max(1, cus);
+DockShape dock_shape(const LaunchWork& wk, int K, int S, int top_k, int cus) {
+    constexpr double kUnit = 8e-5, kChunkFixed = 2.4, kTileFixed = 15.0, kWaveFixed = 0.34, kSelect = 15.0,
+                     kSplitTop = 6.4, kPose = 0.7, kPoseAtom = 0.14, kTail = 0.25,
+                     kTailUnsorted = 0.8, kTailRounds = 0.15, kAlone = 1.6, kShare = 0.01, kIdle = 0.74,
+                     kDispatch = 0.004, kWait = 0.037, kOneOnCu = 1.06;
+    const double n_cu = std::max(1, cus), atoms = (double)wk.n_atoms / std::max(1, wk.n_lig);
     auto chunks_of = [&](int lanes) { return (K * lanes + kWave - 1) / kWave; };
-    auto lds_of = [&](int w, int lanes) { return dock_lds(n_max, rot_max, top_k, w, lanes, S); };
+    auto lds_of = [&](int w, int lanes) { return dock_lds(wk.n_max, wk.rot_max, top_k, w, lanes, S); };
     DockShape best;
     double best_time = -1.0;
     for (int lanes : {4, 8, 16, 32}) {
         if (lanes > S) continue;
-        DockShape sh;
-        sh.lanes = lanes;
         const int chunks = chunks_of(lanes);
-        const int64_t total = (int64_t)n_lig * chunks;
-        // the workgroup size with the most waves on a CU; one workgroup alone on a CU leaves it idle
-        // while it stages and finishes; 5 to 7 waves spread unevenly over the four SIMDs, and a second
-        // such workgroup does not fit beside them (150 ligands of up to 128 atoms: 14.2 ms in
-        // workgroups of 5, 7.6 in workgroups of 4).  Where as many fit, fewer waves wait less for each
-        // other (256 ligands of up to 60 atoms in workgroups of 1, 2 and 4: 718, 750 and 782 us); but
-        // with top_k every workgroup takes part in the selection (4,000 ligands, top 8, in 4 and in 2:
-        // 12.6 and 13.0 ms)
-        double most = -1.0;
-        int on_cu = 1;
+        const double work = kUnit * chunk_work(wk, lanes, S) * kWave / lanes;
+        // workgroups of 5 to 7 waves spread unevenly over the four SIMDs, and a second one does not fit
+        // beside them (150 ligands of up to 128 atoms: 14.2 ms in workgroups of 5, 7.6 in workgroups of 4)
         for (int w : {1, 2, 3, 4, 8}) {
             const int lds = lds_of(w, lanes).total;
             if (w > chunks || lds > kDockLdsBytes) break;
-            const int fit = dock_waves_per_cu(lds, w);
-            const double wait = top_k > 0 ? 1.0 : 1.0 - 0.012 * (w - 1);
-            const double score = (double)chunks / (double)((chunks + w - 1) / w * w) * fit * (fit == w ? 0.8 : 1.0) * wait;
-            if (score >= most) { most = score; sh.waves = w; on_cu = fit; }
+            const int on_cu = dock_waves_per_cu(lds, w);
+            const double groups = n_cu * on_cu / w;   // resident workgroups
+            // waves wait for the workgroup's last; with top_k they have the FP64 poses to share
+            const double chunk = work * std::max(on_cu, 11) / 11.0 * (on_cu == w ? kOneOnCu : 1.0) *
+                                     (top_k > 0 ? 1.0 : 1.0 + kWait * (w - 1)) + kChunkFixed;
+            const double alone = kAlone * (chunk - kChunkFixed) * (1.0 + kShare * (w - 1)) + kChunkFixed;
+            const double top = top_k > 0 ? kSelect + (top_k + w - 1) / w * (kPose + kPoseAtom * atoms) : 0.0;
+            for (int each = 1, last = 0;; each *= 2) {   // chunks of a wave
+                const int parts = (chunks + w * each - 1) / (w * each);
+                if (parts != last) {
+                    const double tiles = (double)(wk.n_lig + wk.beside) * parts;
+                    const double fixed = kTileFixed + kWaveFixed * (w - 1) + (top_k > 0 && parts > 1 ? kSplitTop : 0.0);
+                    const int longest = (chunks + parts * w - 1) / (parts * w);
+                    const double full = (tiles * ((double)chunks / (parts * w) * chunk + fixed) +
+                                         (wk.n_lig + wk.beside) * top) / groups;
+                    const double one = kIdle * (longest * alone + fixed) + top;
+                    const double f2 = full * full, o2 = one * one;
+                    const double time = std::sqrt(std::sqrt(f2 * f2 + o2 * o2)) +
+                                        ((wk.sorted ? kTail : kTailUnsorted) + (tiles >= groups ? kTailRounds * groups / tiles : 0.0)) *
+                                            (longest * chunk + fixed + top) + kDispatch * tiles;
+                    if (best_time < 0.0 || time < best_time) {
+                        best_time = time;
+                        best.lanes = lanes;
+                        best.waves = w;
+                        best.parts = parts;
+                    }
+                    if (parts == 1 || tiles < groups) break;   // fewer workgroups leave more of the chip idle
+                }
+                last = parts;
+            }
         }
-        // few chunks: spread over the CUs first
-        if (total <= 4 * n_cu) sh.waves = std::min(sh.waves, total <= 2 * n_cu ? 1 : 2);
-        const double rounds = (double)(n_lig + beside) * chunks / (double)(n_cu * std::max(1, on_cu));
-        const double time = lane_cost(lanes, S) / lanes * std::max(on_cu, 11) *
-                            std::pow(std::pow(rounds, 4.0) + std::pow(kAloneRounds, 4.0), 0.25);
-        if (best_time >= 0.0 && time >= best_time) continue;
-        best_time = time;
-        // a wave takes a few chunks one after another, fewer than a tenth of the rounds
-        const int each = std::max(1, (int)std::min<double>(rounds / 10.0, chunks));
-        sh.parts = (chunks + sh.waves * each - 1) / (sh.waves * each);
-        best = sh;
     }
     // A turn a lane and most of the chip idle: a second wave counts the clashes while the first looks
     // up.  One ligand of 38 atoms 110 -> 87 us, 4 of up to 60 106 -> 85, 16: 197 -> 168; 16-bit, up to
     // 90 atoms, 13: 233 -> 187, 20: 360 -> 263, 32: 291 -> 303; 64 of 24 atoms at 64 orientations of 16
     // turns 59 -> 49, 100 of them 60 -> 68.  The line is where the pairs, six a CU, are all resident,
-    // with smaller ligands counted by their atoms, for they make room soon.
-    const double full = beside + (double)n_atoms / std::max(1, n_max);
-    if (best.lanes == S && full * chunks_of(S) <= kPairChunks * n_cu &&
-        lds_of(2, S).total <= kDockLdsBytes) {
+    // with smaller ligands counted by their atoms, for they make room soon.  Without bonds to speak of
+    // (16 rigid ligands 57 us, 72 in pairs; with a tenth of the work in bonds 40 235 and 199) the second wave has
+    // nothing to take over.
+    const double all = wk.beside + (double)wk.n_atoms / std::max(1, wk.n_max);
+    if (best.lanes == S && all * chunks_of(S) <= kPairChunks * n_cu && lds_of(2, S).total <= kDockLdsBytes &&
+        32.0 * wk.bonds >= wk.turn + wk.offset + wk.rest) {
         best.pair = true;
         best.waves = 2;
         best.parts = chunks_of(S);
@@ -642,6 +656,7 @@ int exs_upload_ligands(const exs_ligand_batch* in, void* stream, int64_t* batch_
         for (int l = 0; l < L; ++l) {
             b->n_max = std::max<int>(b->n_max, b->info[l].n);
             b->rot_max = std::max<int>(b->rot_max, b->info[l].nrot);
+            b->work.add(b->info[l].n, b->mcount[l].data(), b->info[l].nrot);
         }
         GridDesc* h_grids = reinterpret_cast<GridDesc*>(hb + o_grids);
         for (size_t sl = 0; sl < pk.size(); ++sl) {
@@ -763,6 +778,12 @@ int exs_release_ligands(int64_t batch) {
 
 namespace {
 
+int used_pockets(const Batch& b) {
+    int used = 0;
+    for (int c : b.count_of_slot) used += c > 0 ? 1 : 0;
+    return used;
+}
+
 // Processing order of a persistent launch: work queues laid out by queue_plan (spread or
 // pocket-major); the device array holds the order followed by the queue bounds (kMaxWorkQueues + 1
 // entries reserved) and *n_queues receives their count.  (Plain launches take the upload's order.)
@@ -777,13 +798,11 @@ int batch_order(Batch& b, int K, int S, int P, int T, hipStream_t st, int32_t** 
     }
     std::vector<double> cost(b.L);
     std::vector<int> pocket(b.L), ord(b.L + kMaxWorkQueues + 1);
-    int used = 0;
     for (int l = 0; l < b.L; ++l) {
         cost[l] = ligand_cost(b.info[l].n, b.mcount[l].data(), b.info[l].nrot, K, S, P, T);
         pocket[l] = b.info[l].pocket;
     }
-    for (int c : b.count_of_slot) used += c > 0 ? 1 : 0;
-    const QueuePlan plan = queue_plan(b.L, used, (K + kWave - 1) / kWave);
+    const QueuePlan plan = queue_plan(b.L, used_pockets(b), (K + kWave - 1) / kWave);
     work_queues(b.L, pocket.data(), cost.data(), plan.n_queues, plan.pocket_major, ord.data(), ord.data() + b.L);
     int32_t* d = nullptr;
     HIP_TRY(hipMalloc(&d, ord.size() * sizeof(int32_t)));
@@ -1001,8 +1020,14 @@ void base_args(DockArgs& a, const Batch& b, const exs_search_params& p, const La
 
 // The launch of `count` ligands of batch b, from position `start` of the order.
 int plan_launch(const Batch& b, const exs_search_params& p, const LaunchSettings& ls, int dev, int storage,
-                int start, int count, bool persistent, DockLaunch* out) {
-    out->shape = dock_shape(count, 0, b.L > 0 ? (int64_t)b.A * count / b.L : 0, b.n_max, b.rot_max, p.n_orient, p.torsion_steps, ls.top_k, rt::device_cus(dev));
+                int start, int count, bool sorted, bool persistent, DockLaunch* out) {
+    LaunchWork w = b.work.mean(p.torsion_steps, p.passes, p.n_offsets);   // a launch of some pockets: of all ligands
+    w.n_lig = count;
+    w.sorted = sorted;
+    w.n_atoms = b.L > 0 ? (int64_t)b.A * count / b.L : 0;
+    w.n_max = b.n_max;
+    w.rot_max = b.rot_max;
+    out->shape = dock_shape(w, p.n_orient, p.torsion_steps, ls.top_k, rt::device_cus(dev));
     out->storage = storage;
     out->start = start;
     out->count = count;
@@ -1051,16 +1076,20 @@ int exs_dock_batch(int64_t batch, const exs_search_params* params, void* stream,
         const int L = b->L;
         // the launches, and the floats of pose scratch that the largest of them needs
         std::vector<DockLaunch> launches;
+        const bool pocket_major = persistent && queue_plan(L, used_pockets(*b), (K + kWave - 1) / kWave).pocket_major;
         int64_t scratch_floats = 1;
         for (int gi = 0, start = 0; gi < (int)b->count_of_slot.size();) {
             // pockets of one texel storage share a launch: a launch each left the device idle at the
             // end of every one (2,003 ligands over 3 pockets: 3.8 ms a pass, 2.9 ms in one launch)
             const int st_g = persistent ? ls.storage : b->storage_of_slot[gi];
-            int count = 0;
-            for (; gi < (int)b->count_of_slot.size() && (persistent || b->storage_of_slot[gi] == st_g); ++gi) count += b->count_of_slot[gi];
+            int count = 0, pockets = 0;
+            for (; gi < (int)b->count_of_slot.size() && (persistent || b->storage_of_slot[gi] == st_g); ++gi) {
+                count += b->count_of_slot[gi];
+                pockets += b->count_of_slot[gi] > 0 ? 1 : 0;
+            }
             if (count == 0) continue;
             DockLaunch d;
-            if (int rc = plan_launch(*b, p, ls, dev, st_g, start, count, persistent, &d)) return rc;
+            if (int rc = plan_launch(*b, p, ls, dev, st_g, start, count, persistent ? !pocket_major : pockets <= 1, persistent, &d)) return rc;
             scratch_floats = std::max(scratch_floats, d.slots * d.shape.slot_floats(b->n_max));
             launches.push_back(d);
             start += count;
@@ -1451,7 +1480,7 @@ int noalloc_plan(int64_t batch, const exs_search_params* params, NoAllocPlan* ou
     base_args(out->args, *b, p, ls, nullptr, nullptr, nullptr);
     DockLaunch d;
     if (b->L > 0)
-        if (int rc = plan_launch(*b, p, ls, dev, ls.storage, 0, b->L, true, &d)) return rc;
+        if (int rc = plan_launch(*b, p, ls, dev, ls.storage, 0, b->L, used_pockets(*b) <= 1, true, &d)) return rc;
     DockArgs& a = out->args;
     a.order = b->d_upload_order;
     a.n_order = b->L;

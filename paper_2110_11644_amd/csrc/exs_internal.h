@@ -167,7 +167,47 @@ struct DockShape {
     DockLds lds{};
     int64_t slot_floats(int n_max) const { return kSlotHead + ((int64_t)waves + (parts > 1 ? 1 : 0)) * 3 * n_max; }
 };
-DockShape dock_shape(int n_lig, int beside, int64_t n_atoms, int n_max, int rot_max, int K, int S, int top_k, int cus);
+// What the shape of a launch is chosen by: its ligands, the largest one, and the mean work of one of
+// their orientations (turns, offsets and the rest, in ligand_cost's units).
+struct LaunchWork {
+    int n_lig = 0, beside = 0;   // beside: ligands of another launch on the chip
+    bool sorted = true;          // the ligands come longest first, in every queue
+    int64_t n_atoms = 0;
+    int n_max = 1, rot_max = 0;
+    double turn = 0.0, offset = 0.0, rest = 0.0;
+    double bonds = 0.0;          // of it the bonds': turns and clash pairs
+};
+DockShape dock_shape(const LaunchWork& w, int K, int S, int top_k, int cus);
+
+// Sums over ligands from which the mean work follows for any search settings.
+struct WorkSums {
+    double ligands = 0, atoms = 0, square = 0, moving = 0, pairs = 0;   // square: n^2; moving, pairs: over the bonds
+    void add(int n, const int16_t* m, int nrot) {
+        ligands += 1;
+        atoms += n;
+        square += (double)n * n;
+        for (int b = 0; b < nrot; ++b) {
+            moving += m[b];
+            pairs += (double)m[b] * (n - m[b]);
+        }
+    }
+    void add(const WorkSums& o) {
+        ligands += o.ligands;
+        atoms += o.atoms;
+        square += o.square;
+        moving += o.moving;
+        pairs += o.pairs;
+    }
+    LaunchWork mean(int S, int P, int T) const {
+        LaunchWork w;
+        const double per = ligands > 0 ? 1.0 / ligands : 0.0;
+        w.turn = 40.0 * P * S * moving * per;
+        w.offset = 40.0 * P * (T > 1 ? T : 0) * atoms * per;
+        w.rest = (80.0 * atoms + 20.0 * (square + P * pairs)) * per;
+        w.bonds = w.turn + 20.0 * P * pairs * per;
+        return w;
+    }
+};
 
 // Everything one dock launch reads and writes.
 struct DockArgs {

@@ -139,6 +139,7 @@ struct Request {
     std::vector<uint32_t> ruv;
     std::vector<uint4> rmask;
     std::vector<double> cost;
+    std::vector<WorkSums> work;   // per ligand
     // arena ranges
     int lig0 = 0, atom0 = 0, rot0 = 0;
     int scheduled = 0, remaining = 0;
@@ -424,7 +425,7 @@ int Server::submit(const exs_ligand_batch& in, int64_t* id_out) {
         return rt::fail(EXS_ENOMEM, "request of %d ligands / %d atoms (%lld B) exceeds the server arena "
                         "(%lld B)", L, r->A, (long long)r->bytes, (long long)arena_budget_);
     r->info.resize(L); r->ref.resize(r->A); r->ref64.resize((size_t)r->A * 3); r->excl.resize(r->A);
-    r->ruv.resize(r->R); r->rmask.resize(r->R); r->cost.resize(L);
+    r->ruv.resize(r->R); r->rmask.resize(r->R); r->cost.resize(L); r->work.resize(L);
     r->best_score.resize(L); r->desc.resize(L); r->coords.resize((size_t)r->A * 3);
     PackedLigand pk;            // reused across the request's ligands (keeps its capacity)
     std::string err;
@@ -463,6 +464,7 @@ int Server::submit(const exs_ligand_batch& in, int64_t* id_out) {
             m[b] = (int16_t)pk.moving[b].count();
         }
         r->cost[l] = ligand_cost(n, m.data(), nr, K_, prm_.torsion_steps, prm_.passes, prm_.n_offsets);
+        r->work[l].add(n, m.data(), nr);
     }
     std::lock_guard<std::mutex> lk(mu_);
     if (stop_) return rt::fail(EXS_EINVAL, "server is shutting down");
@@ -523,6 +525,7 @@ bool Server::launch(Iteration& it) {
     std::vector<double> cost;
     std::vector<int> pocket;
     std::vector<int32_t> lig, nat, nrt;
+    WorkSums sums;
     it.work.clear();
     for (Request* r : inflight_) {
         if ((int)lig.size() >= max_iter_) break;
@@ -535,6 +538,7 @@ bool Server::launch(Iteration& it) {
             lig.push_back(r->lig0 + r->scheduled + i);
             nat.push_back(inf.n);
             nrt.push_back(inf.nrot);
+            sums.add(r->work[r->scheduled + i]);
         }
         it.work.push_back({r, r->scheduled, take});
         r->scheduled += take;
@@ -578,7 +582,14 @@ bool Server::launch(Iteration& it) {
     for (int i = 0; i < n_iters_; ++i)
         if (it_[i].running) beside += it_[i].n_lig;
     it.n_lig = n;
-    DockShape sh = dock_shape(n, beside, std::accumulate(nat.begin(), nat.end(), (int64_t)0), n_max, rot_max, K_, prm_.torsion_steps, top_k_, rt::device_cus(dev_));
+    LaunchWork w = sums.mean(prm_.torsion_steps, prm_.passes, prm_.n_offsets);
+    w.n_lig = n;
+    w.beside = beside;
+    w.sorted = !plan.pocket_major;
+    w.n_atoms = std::accumulate(nat.begin(), nat.end(), (int64_t)0);
+    w.n_max = n_max;
+    w.rot_max = rot_max;
+    DockShape sh = dock_shape(w, K_, prm_.torsion_steps, top_k_, rt::device_cus(dev_));
     if (sh.parts > 1)   // a scratch slot per part: as many parts as fit; at one, a slot per workgroup
         sh.parts = (int)std::max<int64_t>(1, std::min<int64_t>(sh.parts, scratch_floats_ / (n * sh.slot_floats(n_max))));
     a.lds = sh.lds;
