@@ -155,7 +155,8 @@ inline DockLds dock_lds(int n_max, int rot_max, int top_k, int waves, int lanes,
     return d;
 }
 constexpr size_t kMaxLdsBytes = 160 * 1024;   // gfx950 LDS per workgroup
-constexpr int kDockLdsBytes = (int)kMaxLdsBytes - 256;   // dynamic LDS beside the dock kernel's static words
+constexpr int kDockStaticLds = 16;                      // the dock kernel's static words
+constexpr int kDockLdsBytes = (int)kMaxLdsBytes - 256;   // dynamic LDS beside them
 // Words in front of a scratch slot's poses: a part's best score, orientation and tau, then its
 // torsions from word 4.
 constexpr int kSlotHead = 4 + kMaxRot;
@@ -246,7 +247,7 @@ struct DockArgs {
     // others.  Null, or n_queues = 1: one queue over the whole order.
     const int32_t* queue_bounds;
     int32_t n_queues;
-    int32_t pad1;
+    int32_t beside;           // persistent launches: another launch may hold the workgroups back
     // outputs (indexed by caller ligand / rotatable-bond index)
     float* orient_score;      // [L*K]
     uint8_t* orient_theta;    // [R*K], element (rot_base+b)*K + k

@@ -606,6 +606,7 @@ bool Server::launch(Iteration& it) {
     a.done = it.d_counter + kMaxWorkQueues;
     a.queue_bounds = d_bounds;
     a.n_queues = plan.n_queues;
+    a.beside = beside > 0 ? 1 : 0;
     a.scratch = it.scratch;
     // each ligand's finish writes its result straight into the pinned result buffer, so the
     // iteration ends with its search (a kernel queued after it would wait for CUs behind the

@@ -42,3 +42,11 @@ def test_split_launches_of_short_searches(B, atoms, rot, count, K, steps, offset
     plain, persistent = times(B, atoms, rot, count, K, steps, offsets, top_k)
     print("plain %.3f ms persistent %.3f ms" % (plain, persistent), flush=True)
     assert plain <= 1.5 * persistent
+
+
+@pytest.mark.parametrize("atoms,rot,count,K,steps,offsets,top_k", [((15, 40), 0, 1000, 33, 32, 1, 0),
+                                                                  ((3, 9), 6, 300, 256, 8, 1, 0)])
+def test_work_queues_of_short_searches(B, atoms, rot, count, K, steps, offsets, top_k):   # noqa: F811
+    plain, persistent = times(B, atoms, rot, count, K, steps, offsets, top_k)
+    print("plain %.3f ms persistent %.3f ms" % (plain, persistent), flush=True)
+    assert persistent <= 1.5 * plain
