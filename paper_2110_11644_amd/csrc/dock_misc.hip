@@ -134,9 +134,12 @@ hipError_t launch_unfold(const LigInfo* info, float4* ref, double* ref64, const 
     if (n_lig <= 0) return hipSuccess;
     UnfoldArgs a{info, ref, ref64, rot_uv, rot_mask, turns, order, n_lig, R, passes, 0};
     switch (S) {
-        case 8: hipLaunchKernelGGL(unfold_kernel<8>, dim3(n_lig), dim3(64), 0, st, a); break;
-        case 16: hipLaunchKernelGGL(unfold_kernel<16>, dim3(n_lig), dim3(128), 0, st, a); break;
-        case 32: hipLaunchKernelGGL(unfold_kernel<32>, dim3(n_lig), dim3(256), 0, st, a); break;
+        case 8: hipLaunchKernelGGL((unfold_kernel<8, 4>), dim3(n_lig), dim3(64), 0, st, a); break;
+        case 16: hipLaunchKernelGGL((unfold_kernel<16, 4>), dim3(n_lig), dim3(128), 0, st, a); break;
+        case 32:
+            if (n_lig >= kUnfoldMany) hipLaunchKernelGGL((unfold_kernel<32, 1>), dim3(n_lig), dim3(64), 0, st, a);
+            else hipLaunchKernelGGL((unfold_kernel<32, 4>), dim3(n_lig), dim3(256), 0, st, a);
+            break;
         default: return hipErrorInvalidValue;
     }
     return hipGetLastError();
