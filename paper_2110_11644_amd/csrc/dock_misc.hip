@@ -112,10 +112,9 @@ hipError_t launch_expand_grid(const float* src, void* dst, int nx, int ny, int n
     return hipGetLastError();
 }
 
-hipError_t launch_rank(const DockArgs& a, int n_lig, const int32_t* order, hipStream_t st) {
+hipError_t launch_rank(const DockArgs& a, int n_lig, int64_t n_atoms, const int32_t* order, hipStream_t st) {
     if (n_lig <= 0) return hipSuccess;
-    // a wave for every 64 poses of a ligand, at most kRankWaves
-    const int waves = std::min(kRankWaves, (a.K + kWave - 1) / kWave);
+    const int waves = rank_waves(n_lig, n_atoms, a.K);
     hipLaunchKernelGGL(rank_kernel, dim3(n_lig), dim3(waves * kWave),
                        (size_t)rank_lds_words(a.K, a.n_max) * sizeof(int), st, a, n_lig, order);
     return hipGetLastError();

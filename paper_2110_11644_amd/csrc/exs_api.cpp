@@ -949,7 +949,7 @@ hipError_t enqueue_dock(const DockArgs& base, const Batch& b, const std::vector<
     }
     if (e == hipSuccess && ev_dock) e = hipEventRecord(ev_dock, st);
     // d_order: every pocket's ligands (or every queue's), longest first, one after another
-    if (e == hipSuccess && base.rank_keep > 0) e = launch_rank(base, b.L, d_order, st);
+    if (e == hipSuccess && base.rank_keep > 0) e = launch_rank(base, b.L, b.A, d_order, st);
     if (e == hipSuccess && ev_rank) e = hipEventRecord(ev_rank, st);
     if (e == hipSuccess && base.rescore2) e = launch_rescore2(base, b.L, d_order, st);
     return e;

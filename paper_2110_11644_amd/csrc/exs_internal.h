@@ -352,7 +352,7 @@ hipError_t launch_unfold(const LigInfo* info, float4* ref, double* ref64, const 
                          int S, int passes, hipStream_t st);
 // Ranking of the final poses of `n_lig` ligands (rank_keep > 0), one block per ligand, the
 // ligands taken in `order` (a permutation of 0..n_lig-1, longest first).
-hipError_t launch_rank(const DockArgs& a, int n_lig, const int32_t* order, hipStream_t st);
+hipError_t launch_rank(const DockArgs& a, int n_lig, int64_t n_atoms, const int32_t* order, hipStream_t st);
 // Second-stage rescoring of the ranked poses of `n_lig` ligands, one block of waves per ligand,
 // the ligands taken in `order`.
 hipError_t launch_rescore2(const DockArgs& a, int n_lig, const int32_t* order, hipStream_t st);
