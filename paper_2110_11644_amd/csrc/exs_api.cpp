@@ -255,11 +255,17 @@ int device_cus(int dev) {
     std::lock_guard<std::mutex> lk(g_dev_mu);
     return g_dev[dev].cus;
 }
-int resident_workgroups(int dev, int storage, int S, const DockShape& sh, int* out) {
-    const void* fn = dock_kernel_fn(storage, S, sh.pair ? 2 * sh.lanes : sh.lanes);
-    if (!fn) return fail(EXS_EINVAL, "no kernel for this configuration");
+// Lets a dock launch of shape sh have its LDS.
+int allow_lds(int storage, int S, const DockShape& sh, const void** fn) {
+    *fn = dock_kernel_fn(storage, S, sh.pair ? 2 * sh.lanes : sh.lanes);
+    if (!*fn) return fail(EXS_EINVAL, "no kernel for this configuration");
     if (sh.lds.total > 64 * 1024)
-        HIP_TRY(hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, sh.lds.total));
+        HIP_TRY(hipFuncSetAttribute(*fn, hipFuncAttributeMaxDynamicSharedMemorySize, sh.lds.total));
+    return EXS_OK;
+}
+int resident_workgroups(int dev, int storage, int S, const DockShape& sh, int* out) {
+    const void* fn = nullptr;
+    if (int rc = allow_lds(storage, S, sh, &fn)) return rc;
     int per_cu = 0;
     hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, fn, sh.waves * kWave, sh.lds.total);
     if (e != hipSuccess || per_cu < 1) per_cu = 1;
@@ -1036,12 +1042,43 @@ int plan_launch(const Batch& b, const exs_search_params& p, const LaunchSettings
     out->count = count;
     out->blocks = count * out->shape.parts;
     out->slots = out->blocks;
-    int resident = 0;
-    if (int rc = rt::resident_workgroups(dev, storage, p.torsion_steps, out->shape, &resident)) return rc;
-    // only what is resident: the others would come when the work is done, and each of them asks every
-    // queue for it (1,000 ligands in 32,000 workgroups: 5.6 ms, 2.9 ms in a plain launch)
-    if (persistent) out->blocks = std::max(1, std::min(out->blocks, resident));
+    const void* fn = nullptr;
+    if (!persistent) {
+        if (int rc = rt::allow_lds(storage, p.torsion_steps, out->shape, &fn)) return rc;
+    } else {
+        // only what is resident: the others would come when the work is done, and each of them asks every
+        // queue for it (1,000 ligands in 32,000 workgroups: 5.6 ms, 2.9 ms in a plain launch)
+        int resident = 0;
+        if (int rc = rt::resident_workgroups(dev, storage, p.torsion_steps, out->shape, &resident)) return rc;
+        out->blocks = std::max(1, std::min(out->blocks, resident));
+    }
     if (out->shape.parts == 1) out->slots = out->blocks;
+    return EXS_OK;
+}
+
+// The launches of a job on batch b, and the floats of pose scratch that the largest of them needs.
+int plan_launches(const Batch& b, const exs_search_params& p, const LaunchSettings& ls, int dev, bool persistent,
+                  std::vector<DockLaunch>* launches, int64_t* scratch_floats) {
+    const bool pocket_major =
+        persistent && queue_plan(b.L, used_pockets(b), (p.n_orient + kWave - 1) / kWave).pocket_major;
+    *scratch_floats = 1;
+    for (int gi = 0, start = 0; gi < (int)b.count_of_slot.size();) {
+        // pockets of one texel storage share a launch: a launch each left the device idle at the
+        // end of every one (2,003 ligands over 3 pockets: 3.8 ms a pass, 2.9 ms in one launch)
+        const int st_g = persistent ? ls.storage : b.storage_of_slot[gi];
+        int count = 0, pockets = 0;
+        for (; gi < (int)b.count_of_slot.size() && (persistent || b.storage_of_slot[gi] == st_g); ++gi) {
+            count += b.count_of_slot[gi];
+            pockets += b.count_of_slot[gi] > 0 ? 1 : 0;
+        }
+        if (count == 0) continue;
+        DockLaunch d;
+        const bool sorted = persistent ? !pocket_major : pockets <= 1;
+        if (int rc = plan_launch(b, p, ls, dev, st_g, start, count, sorted, persistent, &d)) return rc;
+        *scratch_floats = std::max(*scratch_floats, d.slots * d.shape.slot_floats(b.n_max));
+        launches->push_back(d);
+        start += count;
+    }
     return EXS_OK;
 }
 
@@ -1077,27 +1114,8 @@ int exs_dock_batch(int64_t batch, const exs_search_params* params, void* stream,
         j->device = dev; j->batch = b; j->prm = p; j->stream = st;
         j->L = b->L; j->A = b->A; j->R = b->R; j->K = K; j->top_k = top_k;
         const int L = b->L;
-        // the launches, and the floats of pose scratch that the largest of them needs
-        std::vector<DockLaunch> launches;
-        const bool pocket_major = persistent && queue_plan(L, used_pockets(*b), (K + kWave - 1) / kWave).pocket_major;
-        int64_t scratch_floats = 1;
-        for (int gi = 0, start = 0; gi < (int)b->count_of_slot.size();) {
-            // pockets of one texel storage share a launch: a launch each left the device idle at the
-            // end of every one (2,003 ligands over 3 pockets: 3.8 ms a pass, 2.9 ms in one launch)
-            const int st_g = persistent ? ls.storage : b->storage_of_slot[gi];
-            int count = 0, pockets = 0;
-            for (; gi < (int)b->count_of_slot.size() && (persistent || b->storage_of_slot[gi] == st_g); ++gi) {
-                count += b->count_of_slot[gi];
-                pockets += b->count_of_slot[gi] > 0 ? 1 : 0;
-            }
-            if (count == 0) continue;
-            DockLaunch d;
-            if (int rc = plan_launch(*b, p, ls, dev, st_g, start, count, persistent ? !pocket_major : pockets <= 1, persistent, &d)) return rc;
-            scratch_floats = std::max(scratch_floats, d.slots * d.shape.slot_floats(b->n_max));
-            launches.push_back(d);
-            start += count;
-        }
         const bool graph = (p.flags & EXS_FLAG_GRAPH) != 0;
+        std::vector<DockLaunch> launches;   // a plan's graph has its own
         std::shared_ptr<Plan> plan;
         std::vector<int64_t> plan_key;
         if (graph) {
@@ -1121,6 +1139,8 @@ int exs_dock_batch(int64_t batch, const exs_search_params* params, void* stream,
             j->layout = plan->layout;
         } else {
             DockArgs& a = j->args;
+            int64_t scratch_floats = 1;
+            if (int rc = plan_launches(*b, p, ls, dev, persistent, &launches, &scratch_floats)) return rc;
             base_args(a, *b, p, ls, r32, r64, order_k);
             std::shared_ptr<Plan> fresh;
             if (graph) fresh = std::make_shared<Plan>();
