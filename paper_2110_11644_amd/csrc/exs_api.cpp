@@ -1225,13 +1225,21 @@ int exs_get_best_poses(int64_t job, int wait, float* best_score, exs_pose_desc* 
         const size_t coord_bytes = (size_t)j->A * 3 * sizeof(float);
         const bool together = coords && coord_bytes <= (size_t)1 << 18;
         std::vector<unsigned char> head;
-        if (best_score || desc || together) {
+        if (best_score && !desc && !together) {   // the scores alone: a fifth of the arrays' bytes
+            std::vector<double> s64(tk > 0 ? L : 0);
+            if (tk > 0) {
+                if (int rc = copy_out(s64.data(), a.best_score64, s64.size())) return rc;
+                for (int l = 0; l < L; ++l) best_score[l] = (float)s64[l];
+            } else if (int rc = copy_out(best_score, a.best_score, (size_t)L)) {
+                return rc;
+            }
+        } else if (best_score || desc || together) {
             head.resize(together ? y.coords_end : y.coords);
             if (int rc = copy_out(head.data(), dev, head.size())) return rc;
         }
         if (together) memcpy(coords, on_host(head, y.head, a.best_coords), coord_bytes);
         else if (int rc = copy_out(coords, a.best_coords, (size_t)j->A * 3)) return rc;
-        if (best_score || desc) {
+        if (!head.empty() && (best_score || desc)) {
             const float* bs = on_host(head, y.head, a.best_score);
             const int32_t* bk = on_host(head, y.head, a.best_k);
             const int32_t* bt = on_host(head, y.head, a.best_tau);
