@@ -35,6 +35,7 @@
 #include <memory>
 #include <mutex>
 #include <numeric>
+#include <stdexcept>
 #include <string>
 #include <thread>
 #include <unordered_map>
@@ -395,6 +396,9 @@ int Server::create(const int32_t* pockets, int n_pockets, const exs_search_param
     for (int32_t id : pocket_ids_) rt::pocket_use(id, +1);
     thread_ = std::thread([this] {
         try {
+            // a thread starts on device 0; what an iteration asks of the runtime (residency, LDS) is asked of
+            // the current device
+            if (hipError_t e = hipSetDevice(dev_)) throw std::runtime_error(hipGetErrorString(e));
             loop();
         } catch (const std::exception& e) {   // fail the server (pollers see it) rather than the process
             std::lock_guard<std::mutex> lk(mu_);
