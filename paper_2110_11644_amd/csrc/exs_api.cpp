@@ -130,10 +130,10 @@ struct Pocket {
 };
 
 // A job's device arrays, carved from one allocation (a call each was most of a small job's time).
-// What exs_get_best_poses reads lies together: [head, coords) the scores, orientations, taus and
+// What exs_get_best_poses reads lies together: [0, coords) the scores, orientations, taus and
 // torsions, then the coordinates, then [topk, topk_end) the top_k arrays.
 struct JobLayout {
-    size_t head = 0, coords = 0, coords_end = 0, topk = 0, topk_end = 0, total = 0;
+    size_t coords = 0, coords_end = 0, topk = 0, topk_end = 0, total = 0;
 };
 
 // A reusable execution plan of one (batch, settings) pair: device buffers that
@@ -1237,14 +1237,14 @@ int exs_get_best_poses(int64_t job, int wait, float* best_score, exs_pose_desc* 
             head.resize(together ? y.coords_end : y.coords);
             if (int rc = copy_out(head.data(), dev, head.size())) return rc;
         }
-        if (together) memcpy(coords, on_host(head, y.head, a.best_coords), coord_bytes);
+        if (together) memcpy(coords, on_host(head, 0, a.best_coords), coord_bytes);
         else if (int rc = copy_out(coords, a.best_coords, (size_t)j->A * 3)) return rc;
         if (!head.empty() && (best_score || desc)) {
-            const float* bs = on_host(head, y.head, a.best_score);
-            const int32_t* bk = on_host(head, y.head, a.best_k);
-            const int32_t* bt = on_host(head, y.head, a.best_tau);
-            const uint8_t* th = on_host(head, y.head, a.best_theta);
-            const double* b64 = on_host(head, y.head, a.best_score64);
+            const float* bs = on_host(head, 0, a.best_score);
+            const int32_t* bk = on_host(head, 0, a.best_k);
+            const int32_t* bt = on_host(head, 0, a.best_tau);
+            const uint8_t* th = on_host(head, 0, a.best_theta);
+            const double* b64 = on_host(head, 0, a.best_score64);
             for (int l = 0; l < L; ++l) {
                 if (best_score) best_score[l] = tk > 0 ? (float)b64[l] : bs[l];
                 if (!desc) continue;

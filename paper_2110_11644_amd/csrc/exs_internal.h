@@ -38,7 +38,7 @@ struct QueuePlan {
 inline QueuePlan queue_plan(int64_t n_ligands, int n_pockets, int waves_per_ligand) {
     if (n_pockets <= 1) return {1, false};
     const int64_t inflight = kInflightWaves / (waves_per_ligand > 0 ? waves_per_ligand : 1);
-    if (n_pockets >= 2 && n_ligands >= inflight * n_pockets) return {kPocketMajorQueues, true};
+    if (n_ligands >= inflight * n_pockets) return {kPocketMajorQueues, true};
     return {kXcds, false};
 }
 
