@@ -270,7 +270,7 @@ int resident_workgroups(int dev, int storage, int S, const DockShape& sh, int* o
     hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, fn, sh.waves * kWave, sh.lds.total);
     if (e != hipSuccess || per_cu < 1) per_cu = 1;
     // the runtime counts the LDS in bytes, the hardware in granules: a workgroup that finds no room starts
-    // its first tile when the others are done (5,120 tiles of 13 KB: 649 us, 540 without it)
+    // its first tile when the others are done (5,120 tiles of 13 KB: 649 us, 558 without it)
     per_cu = std::max(1, std::min(per_cu, dock_waves_per_cu(sh.lds.total + kDockStaticLds, sh.waves) / sh.waves));
     *out = per_cu * std::max(1, device_cus(dev));
     return EXS_OK;

@@ -34,7 +34,8 @@ struct QueuePlan {
     int n_queues;
     bool pocket_major;
 };
-// Layout for n_ligands ligands over n_pockets distinct pockets, waves_per_ligand waves each.
+// Layout for n_ligands ligands over n_pockets distinct pockets, waves_per_ligand waves each
+// (orientations / 64, whatever the launch's lanes: the threshold is an empirical one in that unit).
 inline QueuePlan queue_plan(int64_t n_ligands, int n_pockets, int waves_per_ligand) {
     if (n_pockets <= 1) return {1, false};
     const int64_t inflight = kInflightWaves / (waves_per_ligand > 0 ? waves_per_ligand : 1);

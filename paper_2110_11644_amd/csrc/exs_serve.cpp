@@ -19,9 +19,10 @@
 //    nor the next iteration wait behind a running kernel);
 //  * completion: a request whose last ligand finished has its results copied
 //    to host buffers and its arena ranges freed.
-// A ligand's result does not depend on what it is batched with (every lane
-// searches its own orientation; tiles hold whole ligands), so a request gives
-// the same answer alone and in the mix.
+// A ligand's result does not depend on what it is batched with, though the mix decides how many
+// lanes search an orientation and how many workgroups share a ligand: every sum runs over its atoms
+// in order in one lane, clashes are counts, and ties go to the lower turn, offset and orientation,
+// whoever finds them.  So a request gives the same answer alone and in the mix.
 #include <hip/hip_runtime.h>
 #include <math.h>
 #include <string.h>
@@ -118,8 +119,9 @@ hipError_t own_queue_stream(int cus, hipStream_t* s) {
 }
 
 // Workgroups whose pose scratch (a pose per orientation) the budget sets aside per iteration, and
-// of which four waves make the default iteration: the part of a budget that is not for requests,
-// as callers size their budgets by it.
+// of which four waves make the default iteration: the part of a budget that is not for requests.
+// The kernels need less (scratch_floats_ is allocated); the amount stays as it is because
+// callers size their budgets by it and the refusals of small ones follow from it.
 int accounted_workgroups(int cus, int lpw, int wpl, int ppl, int top_k, int S) {
     const int lig = lpw * (4896 + (top_k > 0 ? 24 * EXS_MAX_ATOMS : 0)), wave = ppl * S * 256;
     int waves = std::min(lpw * wpl, kMaxWavesPerWg);
