@@ -176,7 +176,7 @@ __global__ void stage_ints_kernel(const int32_t* __restrict__ src, int32_t* __re
                                   int* __restrict__ zero, int nz, int lig, int n_lig,
                                   int32_t* __restrict__ slot) {
     const int t = blockIdx.x * blockDim.x + threadIdx.x;
-    if (t < nz) zero[t] = 0;
+    for (int i = t; i < nz; i += gridDim.x * blockDim.x) zero[i] = 0;   // queues, and a count per split ligand
     for (int i = t; i < n; i += gridDim.x * blockDim.x) dst[i] = src[i];
     for (int j = t; j < n_lig; j += gridDim.x * blockDim.x) slot[src[lig + j]] = j;
 }
