@@ -859,8 +859,8 @@ JobLayout job_layout(DockArgs& a, unsigned char* base, int64_t L, int64_t A, int
     take(a.orient_tau, L * K); align();
     take(a.orient_theta, R * K); align();
     take(a.final_xyz, keep > 0 ? A * 3 * K : 0); align();
-    take(a.tile_counter, kMaxWorkQueues + L);
-    a.done = a.tile_counter + kMaxWorkQueues;
+    take(a.tile_counter, kQueueInts + L);
+    a.done = a.tile_counter + kQueueInts;
     align();
     take(a.scratch, scratch_floats);
     y.total = at;
@@ -935,7 +935,7 @@ hipError_t enqueue_dock(const DockArgs& base, const Batch& b, const std::vector<
     bool parts = false;
     for (const DockLaunch& d : launches) parts = parts || d.shape.parts > 1;
     hipError_t e = hipSuccess;
-    if (persistent || parts) e = launch_zero_ints(base.tile_counter, kMaxWorkQueues + (parts ? b.L : 0), st);
+    if (persistent || parts) e = launch_zero_ints(base.tile_counter, kQueueInts + (parts ? b.L : 0), st);
     for (const DockLaunch& d : launches) {
         if (e != hipSuccess) return e;
         DockArgs a = base;

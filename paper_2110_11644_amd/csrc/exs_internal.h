@@ -28,6 +28,10 @@ constexpr int kXcds = 8;   // accelerator complex dies of an MI355X, each with i
 //    the shared last-level cache (4,000 ligands over 4 pockets of 128^3 x 8, BF16: 12.2 ms, 13.0 in
 //    one such queue, 13.2 spread).
 constexpr int kMaxWorkQueues = kXcds;
+// The queues' counters lie a line apart: what workgroups ask of one line is served one after another,
+// about 10 ns each.
+constexpr int kQueueStride = 32;
+constexpr int kQueueInts = kMaxWorkQueues * kQueueStride;
 constexpr int kPocketMajorQueues = 2;
 constexpr int kInflightWaves = 256 * 4 * 3;   // CUs x SIMDs x dock-kernel waves per SIMD
 struct QueuePlan {
@@ -241,7 +245,7 @@ struct DockArgs {
     // the part's pose [n_max][3], then [waves][n_max][3]
     float* scratch;
     int64_t slot_floats;
-    int32_t* tile_counter;    // persistent launches: next tile of each queue [n_queues]
+    int32_t* tile_counter;    // persistent launches: next tile of each queue [n_queues][kQueueStride]
     int32_t* done;            // parts > 1: finished parts of each position of `order`, zeroed
     // persistent launches: n_queues + 1 positions in `order`, queue q = [qb[q], qb[q+1]);
     // a workgroup takes tiles from queue (its XCD index mod n_queues) first, then from the

@@ -383,7 +383,7 @@ int Server::create(const int32_t* pockets, int n_pockets, const exs_search_param
         Iteration& it = it_[i];
         SRV_TRY(hipEventCreateWithFlags(&it.done, hipEventDisableTiming));
         if ((rc = dev_alloc(dev_bufs_, &it.d_order, 4 * (size_t)max_iter_ + kMaxWorkQueues + 1)) ||
-            (rc = dev_alloc(dev_bufs_, &it.d_counter, (size_t)kMaxWorkQueues + max_iter_)) ||
+            (rc = dev_alloc(dev_bufs_, &it.d_counter, (size_t)kQueueInts + max_iter_)) ||
             (rc = dev_alloc(dev_bufs_, &it.scratch, (size_t)scratch_floats_)))
             return rc;
         // mapped, coherent pinned memory: kernels read and write it over the bus, uncached
@@ -609,7 +609,7 @@ bool Server::launch(Iteration& it) {
     if (sh.parts == 1) blocks = std::min(blocks, scratch_floats_ / a.slot_floats);   // parts > 1: a slot per tile
     blocks = std::max<int64_t>(1, blocks);
     a.tile_counter = it.d_counter;
-    a.done = it.d_counter + kMaxWorkQueues;
+    a.done = it.d_counter + kQueueInts;
     a.queue_bounds = d_bounds;
     a.n_queues = plan.n_queues;
     a.beside = beside > 0 ? 1 : 0;
@@ -624,7 +624,7 @@ bool Server::launch(Iteration& it) {
     a.res_coords = reinterpret_cast<float*>(it.hd_res + res_rec_bytes_);
     a.res_theta = it.hd_res + res_rec_bytes_ + res_coord_bytes_;
     hipError_t e = launch_stage_ints(it.hd_order, it.d_order, 4 * n + kMaxWorkQueues + 1, it.d_counter,
-                                     kMaxWorkQueues + (sh.parts > 1 ? n : 0), n + kMaxWorkQueues + 1, n,
+                                     kQueueInts + (sh.parts > 1 ? n : 0), n + kMaxWorkQueues + 1, n,
                                      res_slot_, it.stream);
     if (e == hipSuccess)
         e = launch_dock(a, storage_, sh, (int)blocks, it.stream);
