@@ -294,9 +294,10 @@ void pocket_use(int32_t id, int delta) {
 
 // Lanes per orientation, waves per workgroup and workgroups per ligand (parts) of a launch: the shape
 // with the shortest estimate of its time.  The estimate's terms, in us, and their constants were fitted
-// to 5,721 launches of 101 workloads (sizes, turns, passes, offsets, top_k, rigid and flexible ligands),
-// each in every shape; its choice takes 4 % longer than the best shape on average, a rule by the
-// chunks' rounds alone 27 %, for it split ligands whose search is short: 1,000 ligands of 3-9
+// to 8,186 launches of 149 workloads (sizes, turns, passes, offsets, top_k, rigid and flexible ligands),
+// each in every shape; its choice takes 4 % longer than the best shape on average and 29 % at most
+// (without kStep 6 % and 70 %), a rule by the chunks' rounds alone 27 %, for it split ligands whose
+// search is short: 1,000 ligands of 3-9
 // atoms 409 us against 246, 4,000 with their best 32 poses 1,392 / 461 (rigid, 15-40 atoms) and
 // 3,839 / 2,201 (20-60 atoms), while 10,000 of up to 12 bonds, whose chunks are long, had the same shape.
 //  * a chunk (64 / lanes orientations): its work (turns, offsets, the rest: ligand_cost's units) with
@@ -305,7 +306,9 @@ void pocket_use(int32_t id, int delta) {
 //  * a workgroup: its longest wave's chunks plus kTileFixed (staging, merging); every one of them has
 //    to be dispatched as well.  With top_k one wave selects and the waves share the FP64 poses.
 //  * the launch: the workgroups' time over the CUs' room for them, or one workgroup alone with the longest
-//    ligand where the chip is not full (the fourth powers fit the times between), and a part of a
+//    ligand where the chip is not full (the fourth powers fit the times between; alone, a bond takes
+//    kStep in every pass however little turns with it: 1,500 ligands of 3-8 atoms 245 us in two waves
+//    of 8 chunks, 137 in four of 4), and a part of a
 //    workgroup's time in which the chip runs empty, more of it where the rounds are few.  Where the ligands
 //    come longest first the last workgroups are short ones; pocket by pocket they are not (2,003
 //    ligands of 13 chunks in 13 and in 7 parts: one pocket 2,117 / 2,134 us, three 2,176 / 2,605).
@@ -314,7 +317,7 @@ void pocket_use(int32_t id, int delta) {
 static double chunk_work(const LaunchWork& w, int lanes, int S) {
     switch (lanes) {
         case 8: return (S == 16 ? 1.3 : 0.97) * w.turn + w.offset + 1.2 * w.rest;
-        case 16: return (S == 32 ? 1.05 : 1.35) * w.turn + 1.25 * w.offset + 1.44 * w.rest;
+        case 16: return 0.95 * w.turn + 1.25 * w.offset + 1.44 * w.rest;
         case 32: return 1.15 * w.turn + 1.1 * w.offset + 1.73 * w.rest;
         default: return w.turn + w.offset + w.rest;
     }
@@ -324,7 +327,7 @@ DockShape dock_shape(const LaunchWork& wk, int K, int S, int top_k, int cus) {
     constexpr double kUnit = 8e-5, kChunkFixed = 2.4, kTileFixed = 15.0, kWaveFixed = 0.34, kSelect = 15.0,
                      kSplitTop = 6.4, kPose = 0.7, kPoseAtom = 0.14, kTail = 0.25,
                      kTailUnsorted = 0.8, kTailRounds = 0.15, kAlone = 1.6, kShare = 0.01, kIdle = 0.74,
-                     kDispatch = 0.004, kWait = 0.037, kOneOnCu = 1.06;
+                     kDispatch = 0.004, kWait = 0.044, kOneOnCu = 1.06, kStep = 10.0;
     const double n_cu = std::max(1, cus), atoms = (double)wk.n_atoms / std::max(1, wk.n_lig);
     auto chunks_of = [&](int lanes) { return (K * lanes + kWave - 1) / kWave; };
     auto lds_of = [&](int w, int lanes) { return dock_lds(wk.n_max, wk.rot_max, top_k, w, lanes, S); };
@@ -344,7 +347,7 @@ DockShape dock_shape(const LaunchWork& wk, int K, int S, int top_k, int cus) {
             // waves wait for the workgroup's last; with top_k they have the FP64 poses to share
             const double chunk = work * std::max(on_cu, 11) / 11.0 * (on_cu == w ? kOneOnCu : 1.0) *
                                      (top_k > 0 ? 1.0 : 1.0 + kWait * (w - 1)) + kChunkFixed;
-            const double alone = kAlone * (chunk - kChunkFixed) * (1.0 + kShare * (w - 1)) + kChunkFixed;
+            const double alone = kAlone * (chunk - kChunkFixed) * (1.0 + kShare * (w - 1)) + kChunkFixed + kStep * wk.steps;
             const double top = top_k > 0 ? kSelect + (top_k + w - 1) / w * (kPose + kPoseAtom * atoms) : 0.0;
             for (int each = 1, last = 0;; each *= 2) {   // chunks of a wave
                 const int parts = (chunks + w * each - 1) / (w * each);

@@ -182,16 +182,19 @@ struct LaunchWork {
     int n_max = 1, rot_max = 0;
     double turn = 0.0, offset = 0.0, rest = 0.0;
     double bonds = 0.0;          // of it the bonds': turns and clash pairs
+    double steps = 0.0;          // bonds taken one after another: of every pass
 };
 DockShape dock_shape(const LaunchWork& w, int K, int S, int top_k, int cus);
 
 // Sums over ligands from which the mean work follows for any search settings.
 struct WorkSums {
     double ligands = 0, atoms = 0, square = 0, moving = 0, pairs = 0;   // square: n^2; moving, pairs: over the bonds
+    double bonds = 0;
     void add(int n, const int16_t* m, int nrot) {
         ligands += 1;
         atoms += n;
         square += (double)n * n;
+        bonds += nrot;
         for (int b = 0; b < nrot; ++b) {
             moving += m[b];
             pairs += (double)m[b] * (n - m[b]);
@@ -203,6 +206,7 @@ struct WorkSums {
         square += o.square;
         moving += o.moving;
         pairs += o.pairs;
+        bonds += o.bonds;
     }
     LaunchWork mean(int S, int P, int T) const {
         LaunchWork w;
@@ -211,6 +215,7 @@ struct WorkSums {
         w.offset = 40.0 * P * (T > 1 ? T : 0) * atoms * per;
         w.rest = (80.0 * atoms + 20.0 * (square + P * pairs)) * per;
         w.bonds = w.turn + 20.0 * P * pairs * per;
+        w.steps = P * bonds * per;
         return w;
     }
 };

@@ -20,7 +20,7 @@ CASES = [
     Case((4, 7, 8), 1, 120, 1, 130, 32, 1, 27, 0, 4, True),
     Case((4, 7, 8), 1, 600, 2, 130, 32, 1, 27, 0, 4, False),
     Case((30, 45, 60), 8, 120, 0, 200, 32, 1, 27, 0, 8, True),
-    Case((30, 45, 60), 8, 25, 1, 200, 32, 1, 27, 0, 16, True),
+    Case((30, 45, 60), 8, 40, 1, 200, 32, 1, 27, 0, 16, True),
     Case((30, 45, 60), 8, 8, 2, 200, 32, 1, 27, 0, 32, True),
     Case((4, 9, 16), 2, 1400, 0, 100, 16, 1, 27, 8, 4, False),
     Case((4, 9, 16), 2, 1400, 1, 100, 8, 1, 1, 3, 4, False),

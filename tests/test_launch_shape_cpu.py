@@ -43,15 +43,17 @@ def shapes(tmp_path_factory):
 
 
 def row(B, ligs, copies, s, top_k, cus=CUS):
-    atoms = square = moving = pairs = 0
+    atoms = square = moving = pairs = bonds = 0
     for lig in ligs:
         m = B.exs_pack_topology(lig, 16)["moving"].sum(1)
         atoms += lig.n
         square += lig.n ** 2
         moving += int(m.sum())
+        bonds += len(lig.rot)
         pairs += int((m * (lig.n - m)).sum())
     return (len(ligs) * copies, float(atoms * copies), max(l.n for l in ligs), max(len(l.rot) for l in ligs),
-            float(square * copies), float(moving * copies), float(pairs * copies), s.n_orient, s.torsion_steps, s.passes,
+            float(square * copies), float(moving * copies), float(pairs * copies),
+            float(bonds * copies), s.n_orient, s.torsion_steps, s.passes,
             s.n_offsets, min(top_k, s.n_orient), cus)
 
 
@@ -74,10 +76,10 @@ def test_limits_of_every_launch(shapes):
         mean = r.uniform(0.4, 1.0) * n_max
         K, steps = r.randint(1, 1024), r.choice([8, 16, 32])
         moving = rot * r.uniform(0.1, 0.5) * mean
-        rows.append((n, float(int(n * mean)), n_max, rot, n * mean * mean, n * moving, n * moving * mean * 0.6, K, steps,
+        rows.append((n, float(int(n * mean)), n_max, rot, n * mean * mean, n * moving, n * moving * mean * 0.6, float(n * rot // 2), K, steps,
                      r.randint(0, 3), r.choice([1, 27]), min(K, r.choice([0, 0, 1, 8, 32])), CUS))
     for a, (lanes, waves, parts, pair) in zip(rows, shapes(rows)):
-        n, K, steps, n_max, rot, top_k = a[0], a[7], a[8], a[2], a[3], a[11]
+        n, K, steps, n_max, rot, top_k = a[0], a[8], a[9], a[2], a[3], a[12]
         chunks = (K * lanes + 63) // 64
         assert lanes in (4, 8, 16, 32) and lanes <= steps, a
         assert waves in (1, 2, 3, 4, 8) and 1 <= parts <= chunks, a
@@ -97,3 +99,14 @@ def test_long_searches_are_split_and_short_ones_whole(shapes):
     s = S.SearchSettings(256, 32, 2, 27)
     got = shapes([row(B, large, 1, s, 0), row(B, short, 100, S.SearchSettings(33, 32, 1, 1), 32)])
     assert got[0][2] >= 16 and got[1][2] == 1, got
+
+
+def test_waves_have_few_chunks_where_bonds_in_turn_bound_them(shapes):
+    # small ligands of several bonds: a chunk is a chain of bonds, however little turns with each, so a
+    # launch that the chip holds at once must not give a wave eight chunks (245 us, 137 with four each)
+    from paper_2110_11644_amd import binding as B
+    wl = S.Workload("x", 41, 1, 1, (48,), 0.5, 8, ("uniform", 3, 8), ("uniform", 0, 12), S.SMALL.search)
+    small = S.make_ligands(wl, 0, 50)
+    got = shapes([row(B, small, 30, S.SearchSettings(256, 16, 2, 1), 0)])
+    lanes, waves, parts, _ = got[0]
+    assert 256 * lanes // 64 <= 6 * waves * parts, got
